@@ -511,7 +511,14 @@ dg_status fit_tiles(dg_plan_* p, int32_t n_b, int box, hipStream_t stream, Queue
     return DG_OK;
 }
 
+// Before lists that a plan keeps are written again: waits for its launches that
+// may still read them, whichever stream they went to.
+void settle(const dg_plan_* p) {
+    if (p->launched) (void)hipDeviceSynchronize();
+}
+
 dg_status rebuild_tiles(dg_plan_* p, int32_t n_b_req, hipStream_t stream) {
+    settle(p);
     const int box = degrid_variant_box_bytes(p->variant);
     const int32_t n_b = std::min<int32_t>(n_b_req, degrid_variant_max_nb(p->variant));
     int64_t plain_tiles = 0;   // tiles of n_b visibilities, before building any
@@ -585,6 +592,7 @@ bool scatter_dense(const dg_desc& d, int64_t n_sub, int64_t n_vis, const OwnerTa
 // The work order of 'uvw' and, with 'gridding', the order and tasks of the
 // owner-computes adjoint.
 dg_status build_order(dg_plan_* p, const double* uvw, bool gridding, hipStream_t stream) {
+    settle(p);
     free_owner(p);
     const dg_desc& d = p->desc;
     const size_t n = (size_t)p->offsets.back(), ob = p->offsets.size() * sizeof(int64_t);
