@@ -102,7 +102,9 @@ __global__ __launch_bounds__(kBlockThreads, 2) void degrid_noalloc_kernel(Proble
     const int q = (int)blockIdx.x % nq;
     const int end = (int)((int64_t)n_tiles * (q + 1) / nq);
     const int stride = (((int)gridDim.x - q + nq - 1) / nq) * kWavesPerBlock;
-    int t = uniform((int)((int64_t)n_tiles * q / nq) + ((int)blockIdx.x / nq) * kWavesPerBlock + wv);
+    const int begin = (int)((int64_t)n_tiles * q / nq);
+    const int rank = ((int)blockIdx.x / nq) * kWavesPerBlock + wv;
+    int t = uniform(begin + min(rank, end - begin));
 
     // Subgrid, first visibility and count of tile t: the subgrid is the last
     // one whose first tile is at most t (empty subgrids share theirs with the
@@ -151,7 +153,7 @@ __global__ __launch_bounds__(kBlockThreads, 2) void degrid_noalloc_kernel(Proble
 
         const char* sub_base = static_cast<const char*>(pr.subgrids) + s * (int64_t)pr.sub_bytes;
         const __amdgpu_buffer_rsrc_t ra = make_rsrc(sub_base, pr.sub_bytes);
-        t += stride;
+        t = next_dealt(t, stride, end);
         if (t < end) {
             locate(t, sub, beg, count);
             request();

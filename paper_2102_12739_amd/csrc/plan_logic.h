@@ -95,6 +95,10 @@ struct StaticDeal {
     int32_t stride[kMaxQueues];   // wavefronts serving queue q
 };
 
+// The tile after t of a share that takes every stride-th tile below end, or end
+// when there is none (t + stride need not fit an int).
+constexpr int next_dealt(int t, int stride, int end) { return end - t > stride ? t + stride : end; }
+
 StaticDeal deal_static(const QueueSpec& q, int blocks, int waves_per_block);
 
 }  // namespace dg
