@@ -87,7 +87,7 @@ __global__ __launch_bounds__(kBlockThreads) void grid_adjoint_kernel(LaunchParam
             if (bx1 >= 0) {
                 bw = bx1 - bx0 + kSupportUV;
                 bh = by1 - by0 + kSupportUV;
-                bp = bw + ((8 - bw) & 15);
+                bp = scatter_box_pitch(bw, bh, (int)((uint32_t)BOX / kCell));
                 staged = (uint32_t)(bp * bh) * kCell <= (uint32_t)BOX;
             }
         }

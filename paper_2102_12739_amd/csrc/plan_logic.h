@@ -95,6 +95,16 @@ struct StaticDeal {
     int32_t stride[kMaxQueues];   // wavefronts serving queue q
 };
 
+// Cells from one row of the scatter adjoint's box to the next: the width, rounded
+// up to 8 modulo 16 cells (rows then start on different LDS banks) where the box
+// still fits max_cells with that. Tiles are cut to boxes of bw * bh cells, and a
+// box that does not fit sends 512 atomics per visibility to memory (1.0 M uniform
+// visibilities on 16 subgrids sorted for degridding: 384 us, always padded 8940).
+constexpr int scatter_box_pitch(int bw, int bh, int max_cells) {
+    const int padded = bw + ((8 - bw) & 15);
+    return padded * bh <= max_cells ? padded : bw;
+}
+
 // The tile after t of a share that takes every stride-th tile below end, or end
 // when there is none (t + stride need not fit an int).
 constexpr int next_dealt(int t, int stride, int end) { return end - t > stride ? t + stride : end; }
