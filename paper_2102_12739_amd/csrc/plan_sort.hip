@@ -235,29 +235,36 @@ __global__ __launch_bounds__(256) void write_tiles_kernel(const FitChunk* chunks
     });
 }
 
-// Queue c ends after the first tile with which the visibilities so far, times
-// the number of queues, reach (c + 1) n_vis. The tiles cover the work order
-// without gaps, so those before tile t number tiles[t].begin.
+// The queues of split_queues for such a list. Queue c ends after the first tile
+// with which the visibilities so far, times the number of queues, reach (c + 1)
+// n_vis, but holds at least one tile if there is one left. The tiles cover the
+// work order without gaps, so those before tile t number tiles[t].begin.
 __global__ void tile_queues_kernel(const Tile* tiles, int64_t n_tiles, int64_t n_vis, QueueSpec* q) {
+    __shared__ int32_t full[kMaxQueues];
     const int nq = n_tiles < kMaxQueues ? (int)n_tiles : kMaxQueues;
     const int c = (int)threadIdx.x;
-    if (c >= nq) return;
-    int64_t lo = 0, hi = n_tiles;   // first tile count at which queue c is full
-    if (c < nq - 1) {
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) >> 1;
-            const int64_t sum = tiles[mid].begin + tiles[mid].count;
-            if (sum * nq >= n_vis * (c + 1)) hi = mid; else lo = mid + 1;
+    if (c < nq) {
+        int64_t lo = 0, hi = n_tiles;   // first tile count at which queue c is full
+        if (c < nq - 1) {
+            while (lo < hi) {
+                const int64_t mid = (lo + hi) >> 1;
+                const int64_t sum = tiles[mid].begin + tiles[mid].count;
+                if (sum * nq >= n_vis * (c + 1)) hi = mid; else lo = mid + 1;
+            }
+            ++lo;
+        } else {
+            lo = n_tiles;
         }
-        ++lo;
-    } else {
-        lo = n_tiles;
+        full[c] = (int32_t)lo;
     }
-    q->end[c] = (int32_t)lo;
-    if (c + 1 < nq) q->begin[c + 1] = (int32_t)lo;
-    if (c == 0) {
-        q->n_queues = nq;
-        q->begin[0] = 0;
+    __syncthreads();
+    if (c != 0) return;
+    q->n_queues = nq;
+    int32_t at = 0;
+    for (int k = 0; k < kMaxQueues; ++k) {
+        q->begin[k] = k < nq ? at : 0;
+        if (k < nq) at = (int32_t)min(n_tiles, (int64_t)max(full[k], at + 1));
+        q->end[k] = k < nq ? at : 0;
     }
 }
 
