@@ -26,21 +26,6 @@ __device__ __forceinline__ int xcc_id() {
 
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
-// Copy of a value that the compiler knows to be the same on every lane (it
-// lives in scalar registers). Used for the per-tile descriptors loaded from
-// memory, so that addresses and buffer resources built from them stay scalar.
-template <class T>
-__device__ __forceinline__ T uniform_copy(const T& x) {
-    static_assert(sizeof(T) % 4 == 0, "word-sized types only");
-    uint32_t w[sizeof(T) / 4];
-    __builtin_memcpy(w, &x, sizeof(T));
-#pragma unroll
-    for (unsigned i = 0; i < sizeof(T) / 4; ++i) w[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)w[i]);
-    T y;
-    __builtin_memcpy(&y, w, sizeof(T));
-    return y;
-}
-
 // Orders this wavefront's LDS accesses around a hand-off between its lanes.
 // LDS operations of one wavefront execute in order; this keeps the compiler
 // from moving accesses across the hand-off.
@@ -518,7 +503,6 @@ __device__ __forceinline__ void wave_bbox(bool valid, int x, int y, int& x0, int
 // Scalar-cache view of read-only data: loads through it with a wave-uniform
 // address become scalar loads.
 typedef const __attribute__((address_space(4))) float* ConstF32Ptr;
-typedef const __attribute__((address_space(4))) uint32_t* ConstU32Ptr;
 typedef uint32_t U32x2 __attribute__((ext_vector_type(2)));
 typedef const __attribute__((address_space(4))) U32x2* ConstU32x2Ptr;
 typedef const __attribute__((address_space(4))) Tile* ConstTilePtr;
@@ -794,7 +778,7 @@ __device__ __forceinline__ RowW<G, F> load_row(uint32_t w, __amdgpu_buffer_rsrc_
 // of registers. With one lane per tap, where a visibility's 64 products meet
 // across the whole wavefront and the tile's weights wait in registers, 3.0 M
 // visibilities took 250 us instead of 230 (16-bit storage: 220 instead of 193;
-// 300 000 on a stack of 8 w planes: 289 instead of 240); with this mapping and
+// 300 000 on a stack of 16 w planes: 289 instead of 240); with this mapping and
 // one set of registers for the cells, 241 (203).
 //
 // Weights: from LDS boxes the gather leaves the vector-memory path to them, so

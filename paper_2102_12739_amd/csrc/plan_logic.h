@@ -39,6 +39,8 @@ std::vector<Tile> build_tiles(int64_t n_sub, const int64_t* off, int nb, uint16_
 // Marker of a visibility whose neighbourhood leaves its subgrid.
 constexpr uint32_t kNoStart = 0xFFFFFFFFu;
 
+// (Host form of a cut that the library makes on the device, in chunks and with
+// its own rule for sparse runs: cut_chunk in plan_sort.hip. Only tests call it.)
 // Like build_tiles, but cut where a tile's cells stop fitting a staging box:
 // start[p] is the first tap (y0 << 16 | x0) of the visibility at position p
 // of the work order, or kNoStart. A tile grows while the bounding box of its
@@ -53,6 +55,8 @@ std::vector<Tile> build_tiles_fitted(int64_t n_sub, const int64_t* off, const ui
                                      int support, int64_t cap_cells, int min_fit, uint16_t problem,
                                      int pad_to = 0);
 
+// (Only tests call this one: the adjoint's order is made on the device, by bands
+// of rows.)
 // Which visibilities reach which output block: block b of subgrid s covers
 // cells [by * B, by * B + B) x [bx * B, bx * B + B) (b = (s * nby + by) * nbx + bx,
 // nby = n_v / B, nbx = n_u / B). items[offsets[b] .. offsets[b+1]) are the
