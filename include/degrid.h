@@ -240,12 +240,11 @@ dg_status degrid_residual(dg_plan p, const void* subgrids, const void* g_uv, con
  *   accumulate   0: the output is overwritten; 1: contributions are added to
  *                its current contents.
  * On a plan with a work order (degrid_plan_sort), every cell of the output
- * is summed by one wavefront and written once, so the result has the same
+ * is summed in a fixed order and written once, so the result has the same
  * bits on every call; visibilities whose coordinates
  * moved since the sort are added by a second pass with float32 atomics (so
  * when some moved, their sums' last bits vary from run to run). On
- * a plan in input order, and on small dense subgrids whose sides are not
- * multiples of 16, the output is zeroed (by a kernel) and contributions
+ * a plan in input order the output is zeroed (by a kernel) and contributions
  * are added with float32 atomics, so the last bits vary from run to run.
  * Asynchronous on 'stream'; allocates nothing.
  */

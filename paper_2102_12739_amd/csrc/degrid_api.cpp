@@ -215,11 +215,16 @@ struct dg_plan_ {
     int64_t* d_offsets = nullptr;
     uint64_t version = 0;         // bumped when tiles or work order change
     // owner-computes adjoint (built by degrid_plan_sort)
-    void* own_lists = nullptr;          // the three below, in one allocation
+    void* own_lists = nullptr;          // the five below, in one allocation
     OwnerPlaces* d_places = nullptr;    // positions in the owner order per visibility
     OwnerTask* d_tasks = nullptr;
+    OwnerSlice* d_slices = nullptr;     // of the heavy tasks
+    uint32_t* d_first_slice = nullptr;
     Ctl* d_own_ctl = nullptr;
-    OwnerRecord* d_records = nullptr;   // workspace of the adjoint, per position of the owner order
+    void* own_space = nullptr;          // workspace of the adjoint: the two below
+    OwnerRecord* d_records = nullptr;   // per position of the owner order
+    char* d_partials = nullptr;         // columns of the slices
+    OwnerCounts own_counts{};
     int64_t own_tasks = 0;              // 0: no owner order, the adjoint scatters
     OwnerShape own{};
     size_t max_lds = 0;                 // the device's LDS bytes per workgroup
@@ -229,12 +234,16 @@ namespace {
 
 void free_owner(dg_plan_* p) {
     if (p->own_lists) (void)hipFree(p->own_lists);
-    if (p->d_records) (void)hipFree(p->d_records);
+    if (p->own_space) (void)hipFree(p->own_space);
     p->own_lists = nullptr;
     p->d_places = nullptr;
     p->d_tasks = nullptr;
+    p->d_slices = nullptr;
+    p->d_first_slice = nullptr;
     p->d_own_ctl = nullptr;
+    p->own_space = nullptr;
     p->d_records = nullptr;
+    p->d_partials = nullptr;
     p->own_tasks = 0;
 }
 
@@ -576,19 +585,6 @@ int32_t owner_segment(int64_t rows_of_tasks, int32_t n_u, int64_t n_cu) {
     return 16;
 }
 
-// Whether scattering beats the owner-computes adjoint: its heaviest task, one
-// wavefront's, takes about 0.1 us for each of its visibilities, while dense
-// tiles scatter through their boxes at a few atomics per visibility. 3 subgrids
-// of 99 x 156 with 400 000 visibilities (heaviest 10 400): 1042 us, scattered
-// 112; of 188 x 162 with 100 000 (1395) 156 and 87; 2 of 188 x 162 with 30 000
-// (695, half a visibility per cell) 87 and 101; 8 of 283 x 266 with 400 000
-// (1669, 0.7 per cell) 188 and 540. Subgrids of whole 16 x 16 blocks stay with
-// the owners, whose sums are the same on every run; deep ones have no boxes.
-bool scatter_dense(const dg_desc& d, int64_t n_sub, int64_t n_vis, const OwnerTask& heaviest) {
-    if (d.n_w != kSupportW || (d.n_v % 16 == 0 && d.n_u % 16 == 0)) return false;
-    return heaviest.end - heaviest.begin >= 1200u && 10 * n_vis >= 9 * n_sub * (int64_t)d.n_v * d.n_u;
-}
-
 // The work order of 'uvw' and, with 'gridding', the order and tasks of the
 // owner-computes adjoint.
 dg_status build_order(dg_plan_* p, const double* uvw, bool gridding, hipStream_t stream) {
@@ -627,26 +623,26 @@ dg_status build_order(dg_plan_* p, const double* uvw, bool gridding, hipStream_t
         e = hipStreamSynchronize(stream);
         return e == hipSuccess ? DG_OK : hip_fail(e, "sorting the work order");
     }
-    const size_t tb = (size_t)h.tasks() * sizeof(OwnerTask);
-    e = hipMalloc(&p->own_lists, sizeof(Ctl) + tb + n * sizeof(OwnerPlaces));
+    const size_t tb = (size_t)h.tasks() * sizeof(OwnerTask), pb = n * sizeof(OwnerPlaces);
+    const size_t sb = (size_t)h.slices() * sizeof(OwnerSlice), fb = (size_t)(h.slices() + 1) * sizeof(uint32_t);
+    e = hipMalloc(&p->own_lists, sizeof(Ctl) + tb + sb + pb + fb);
     if (e != hipSuccess) { p->own_lists = nullptr; return hip_fail(e, "hipMalloc(gridding order)"); }
-    p->d_own_ctl = static_cast<Ctl*>(p->own_lists);
-    p->d_tasks = reinterpret_cast<OwnerTask*>(p->d_own_ctl + 1);
-    p->d_places = reinterpret_cast<OwnerPlaces*>(reinterpret_cast<char*>(p->d_tasks) + tb);
-    int64_t n_items = 0;
+    char* at = static_cast<char*>(p->own_lists);
+    p->d_own_ctl = reinterpret_cast<Ctl*>(at);
+    p->d_tasks = reinterpret_cast<OwnerTask*>(at + sizeof(Ctl));
+    p->d_slices = reinterpret_cast<OwnerSlice*>(at + sizeof(Ctl) + tb);
+    p->d_places = reinterpret_cast<OwnerPlaces*>(at + sizeof(Ctl) + tb + sb);
+    p->d_first_slice = reinterpret_cast<uint32_t*>(at + sizeof(Ctl) + tb + sb + pb);
     e = hipMemsetAsync(p->d_own_ctl, 0, sizeof(Ctl), stream);
     if (e == hipSuccess)
-        e = build_owner_order(h, p->d_offsets, p->d_plan_start, p->d_places, p->d_tasks, &n_items, temp, stream);
-    OwnerTask heaviest{};
-    if (e == hipSuccess) e = hipMemcpyAsync(&heaviest, p->d_tasks, sizeof heaviest, hipMemcpyDeviceToHost, stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
+        e = build_owner_order(h, p->d_offsets, p->d_plan_start, p->d_places, p->d_tasks, p->d_slices, p->d_first_slice,
+                              &p->own_counts, temp, stream);
     if (e != hipSuccess) return hip_fail(e, "ordering the adjoint");
-    if (scatter_dense(d, p->n_sub, (int64_t)n, heaviest)) {
-        free_owner(p);
-        return DG_OK;
-    }
-    e = hipMalloc(&p->d_records, std::max<size_t>(1, (size_t)n_items) * sizeof(OwnerRecord));
-    if (e != hipSuccess) { p->d_records = nullptr; return hip_fail(e, "hipMalloc(records)"); }
+    const size_t rb = std::max<size_t>(1, (size_t)p->own_counts.n_items) * sizeof(OwnerRecord);
+    e = hipMalloc(&p->own_space, rb + (size_t)p->own_counts.columns * kOwnerColumnBytes);
+    if (e != hipSuccess) { p->own_space = nullptr; return hip_fail(e, "hipMalloc(gridding workspace)"); }
+    p->d_records = static_cast<OwnerRecord*>(p->own_space);
+    p->d_partials = static_cast<char*>(p->own_space) + rb;
     p->own_tasks = h.tasks();
     return DG_OK;
 }
@@ -812,7 +808,12 @@ dg_status grid_adjoint(dg_plan p, const void* vis, const void* g_uv, const void*
         op.prob = problem_of(p, nullptr, g_uv, g_w, uvw, const_cast<void*>(vis), subgrids_out);
         op.records = p->d_records;
         op.tasks = p->d_tasks;
+        op.slices = p->d_slices;
+        op.first_slice = p->d_first_slice;
+        op.partials = p->d_partials;
         op.n_tasks = p->own_tasks;
+        op.n_split = p->own_counts.n_split;
+        op.n_slices = p->own_counts.n_slices;
         op.ctl = p->d_own_ctl;
         op.accumulate = accumulate;
         op.nby = p->own.nby;

@@ -5,6 +5,8 @@
 #include <stdint.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "plan_logic.h"
 
 namespace dg {
@@ -113,11 +115,56 @@ struct OwnerTask {
 };
 static_assert(sizeof(OwnerTask) == 16, "OwnerTask must stay 16 bytes");
 
+// A task's run takes one wavefront about 0.1 us per visibility, so on plans whose
+// longest run is much longer than an even share, runs are cut into slices, one
+// wavefront each. A slice writes the columns it reaches to a workspace
+// ([kOwnerBand rows][width][4 w values] complex64), and the join pass adds a task's
+// slices in their order and writes the segment.
+//
+// With W = places times slabs: runs are cut where the longest exceeds W /
+// kOwnerEven + kOwnerJoin. W / 2844 is a wavefront's even share of all runs at 16
+// per CU, where a visibility takes 0.23 us, and kOwnerJoin (15 us) stands for the
+// workspace and the join. 8 subgrids of 283 x 266 with 400 000 visibilities (longest
+// about 450) 71 us whole, 121 cut; 3 of 430 x 176 with 400 000 (1150) 135 and 93; 3
+// of 188 x 162 with 100 000 (700) 87 and 46. Longest slice: the larger of
+// kOwnerMinSlice and W / kOwnerSlices, whole batches of 64 (60 000 visibilities on
+// one spot: 44 us with 128, 50 with 256; 1.0 M dense at the centres of 16 subgrids:
+// 169 us with W / 2048, 225 with W / 1024). At most kOwnerMaxSlices can come of that:
+// the runs are together at most 2 W (a window reaches two segments at most), and
+// cutting adds at most one slice per run longer than a slice.
+constexpr int kOwnerMinSlice = 128;
+constexpr int kOwnerSlices = 2048;
+constexpr int kOwnerMaxSlices = 4 * kOwnerSlices;
+constexpr int kOwnerEven = 1280;
+constexpr int kOwnerJoin = 150;
+struct alignas(16) OwnerSlice {
+    uint32_t begin, end;   // positions of the owner order
+    int32_t band;          // subgrid * nby + band
+    int32_t slab;
+    int32_t x_lo, width;   // columns (x_lo a multiple of 8)
+    uint32_t column;       // columns of the slices before it
+    int32_t task;          // index of its task
+};
+static_assert(sizeof(OwnerSlice) == 32, "OwnerSlice must stay 32 bytes");
+constexpr size_t kOwnerColumnBytes = (size_t)kOwnerBand * kSupportW * 8;   // of a slice's workspace
+
+// What the tasks of a plan came to.
+struct OwnerCounts {
+    int64_t n_items;      // places of the owner order
+    int64_t columns;      // of all slices
+    int32_t n_split;      // tasks cut into slices: the first of the list
+    int32_t n_slices;
+};
+
 struct OwnerParams {
     Problem prob;                  // g_uv, g_w, vis (input), grid_out
     const OwnerRecord* records;    // from the record pass
-    const OwnerTask* tasks;        // heaviest first
+    const OwnerTask* tasks;        // heaviest first, n_split of them in slices
+    const OwnerSlice* slices;      // by task and position
+    const uint32_t* first_slice;   // per split task, and the end
+    char* partials;                // the slices' workspace
     int64_t n_tasks;
+    int32_t n_split, n_slices;
     Ctl* ctl;
     int32_t accumulate;            // 1: add to grid_out, 0: overwrite
     int32_t nby;                   // bands per subgrid
@@ -156,8 +203,9 @@ constexpr int kD1Variant = 6;
 hipError_t launch_loss_sum(const double* tile_loss, int64_t n_tiles, double* loss, hipStream_t stream);
 // *p = v (one float64 written by a kernel, so that graphs may capture it).
 hipError_t launch_set_f64(double* p, double v, hipStream_t stream);
-// Owner-computes adjoint: every output cell written once. n_cu and max_lds:
-// the device's compute units and LDS bytes per workgroup.
+// Owner-computes adjoint: every output cell written once (a second launch joins
+// the slices, if there are any). n_cu and max_lds: the device's compute units and
+// LDS bytes per workgroup.
 hipError_t launch_grid_owner(const OwnerParams& p, int gcf_kind, int n_cu, size_t max_lds, hipStream_t stream);
 // Record pass of the adjoint: the records of every visibility, the
 // out-of-range count into ctl, and the number whose first tap differs from
@@ -233,16 +281,19 @@ hipError_t sort_visibilities(const Problem& pr, const int64_t* offsets_host, con
                              uint32_t* perm, uint32_t* plan_start, uint32_t* start, DeviceTemp& temp,
                              hipStream_t stream);
 // The owner order of the adjoint and its tasks, from the first taps: places
-// [n_vis] and tasks[shape.tasks()], heaviest first. *n_items receives the
-// number of positions. Uses 'temp'; synchronises 'stream'.
+// [n_vis] and tasks[shape.tasks()], heaviest first; the slices [shape.slices()]
+// of the heavy ones and first_slice [shape.slices() + 1]. *counts receives what
+// there is of them. Uses 'temp'; synchronises 'stream'.
 struct OwnerShape {
     int64_t n_sub, n_vis;
     int32_t nby, n_u, segment, n_seg, n_slabs;
     int64_t tasks() const { return n_sub * nby * n_seg * n_slabs; }
+    // room for slices (a visibility has two places, each reaches two segments)
+    int64_t slices() const { return std::min<int64_t>(kOwnerMaxSlices, 8 * n_vis * n_slabs / kOwnerMinSlice + 1); }
 };
 hipError_t build_owner_order(const OwnerShape& shape, const int64_t* offsets, const uint32_t* plan_start,
-                             OwnerPlaces* places, OwnerTask* tasks, int64_t* n_items, DeviceTemp& temp,
-                             hipStream_t stream);
+                             OwnerPlaces* places, OwnerTask* tasks, OwnerSlice* slices, uint32_t* first_slice,
+                             OwnerCounts* counts, DeviceTemp& temp, hipStream_t stream);
 hipError_t degrid_kernel_occupancy(int grid_kind, int gcf_kind, int variant, int* blocks_per_cu);
 hipError_t adjoint_kernel_occupancy(int gcf_kind, int variant, int* blocks_per_cu);
 int degrid_variant_count();

@@ -170,13 +170,14 @@ __global__ __launch_bounds__(kBlockThreads) void grid_adjoint_kernel(LaunchParam
 // Owner-computes adjoint
 // ---------------------------------------------------------------------------
 //
-// Three launches. The record pass reads the visibilities in input order and
+// Three launches, or four. The record pass reads the visibilities in input order and
 // writes what the sums need of each (first tap, table rows, value: 16 bytes)
 // at its places in the owner order. The owner pass sums and writes every
 // output cell once with plain stores: no global atomics, and the sums do not
-// depend on timing. A visibility whose first tap at run time differs from the
-// plan's is skipped there; the fix-up pass adds those with atomics and ends
-// at once when there are none.
+// depend on timing. Where visibilities crowd a few segments, a segment's are shared
+// by several wavefronts (slices), and the join pass adds what they wrote. A
+// visibility whose first tap at run time differs from the plan's is skipped there;
+// the fix-up pass adds those with atomics and ends at once when there are none.
 //
 // Owner pass. The output is cut into bands of kOwnerBand rows (and up to four
 // w planes), and bands into segments of columns. A wavefront takes a segment
@@ -221,6 +222,7 @@ __global__ __launch_bounds__(kBlockThreads) void grid_adjoint_kernel(LaunchParam
 typedef float F32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t U32x4 __attribute__((ext_vector_type(4)));
 typedef const __attribute__((address_space(4))) OwnerTask* ConstOwnerTaskPtr;
+typedef const __attribute__((address_space(4))) OwnerSlice* ConstOwnerSlicePtr;
 
 constexpr int kOwnerMaxWaves = 16;                 // one workgroup per CU, four wavefronts per SIMD
 constexpr int kOwnerRec = kSupportW * 2;           // values of c per visibility
@@ -362,34 +364,63 @@ __global__ __launch_bounds__(kOwnerMaxWaves* kWave) void grid_owner_kernel(Owner
     }
     __syncthreads();
 
-    // Tasks come heaviest first and are dealt to the launch's wavefronts back
-    // and forth, those of one workgroup far apart: no atomic. (Claimed one by
-    // one from the queues' cursors, they waited up to 30 us for the atomics.)
+    // Slices come first, then the other tasks, heaviest first, and are dealt to the
+    // launch's wavefronts back and forth, those of one workgroup far apart: no
+    // atomic. (Claimed one by one from the queues' cursors, they waited up to 30 us
+    // for the atomics.)
     const int64_t n_waves = (int64_t)gridDim.x * waves;
     const int64_t me = (int64_t)wv * gridDim.x + blockIdx.x;
-    for (int64_t r0 = 0; r0 < P.n_tasks; r0 += n_waves) {
+    const int64_t n_runs = P.n_tasks - P.n_split + P.n_slices;
+    for (int64_t r0 = 0; r0 < n_runs; r0 += n_waves) {
         const int64_t t = uniform((int)((r0 / n_waves) & 1)) ? r0 + n_waves - 1 - me : r0 + me;
-        if (t >= P.n_tasks) continue;
-        const ConstOwnerTaskPtr tp = (ConstOwnerTaskPtr)uniform_u64((uint64_t)P.tasks) + t;
-        const uint32_t begin = tp->begin, end = tp->end;
-        const int band = tp->band;
-        const int seg = DEEP ? tp->place / P.n_slabs : tp->place;
-        const int slab = DEEP ? tp->place - seg * P.n_slabs : 0;
-        const int s = band / P.nby;
-        const int row0 = (band - s * P.nby) * kOwnerBand;
-        const int x_lo = seg * P.segment;                              // the segment's columns
-        const int width = min(P.segment, pr.n_u - x_lo);
-        const int planes = DEEP ? min(kSupportW, pr.n_w - kSupportW * slab) : kSupportW;
-        // the subgrid's output; rows past its end fall outside the resource
-        float* out = static_cast<float*>(pr.grid_out) + 2 * (int64_t)s * pr.cells_per_sub;
-        const __amdgpu_buffer_rsrc_t ro = make_rsrc(out, (uint32_t)(pr.cells_per_sub * 8));
-        const uint32_t cell_bytes = (uint32_t)pr.n_w * 8u;
+        if (t >= n_runs) continue;
+        const bool slice = t < P.n_slices;
+        uint32_t begin, end;
+        int band, slab = 0, x_lo, width;   // the columns
+        int planes = kSupportW, n_u = pr.n_u, row_out = 0;
+        uint32_t cell_bytes, out_bytes;
+        char* out;
+        int accumulate = 0;
+        if (slice) {
+            const ConstOwnerSlicePtr sp = (ConstOwnerSlicePtr)uniform_u64((uint64_t)P.slices) + t;
+            begin = sp->begin;
+            end = sp->end;
+            band = sp->band;
+            if (DEEP) slab = sp->slab;
+            x_lo = sp->x_lo;
+            width = sp->width;
+            n_u = width;
+            cell_bytes = kSupportW * 8u;
+            out = P.partials + (int64_t)sp->column * (int64_t)kOwnerColumnBytes;
+            out_bytes = (uint32_t)width * (uint32_t)kOwnerColumnBytes;
+        } else {
+            const ConstOwnerTaskPtr tp = (ConstOwnerTaskPtr)uniform_u64((uint64_t)P.tasks) + (t - P.n_slices + P.n_split);
+            begin = tp->begin;
+            end = tp->end;
+            band = tp->band;
+            const int seg = DEEP ? tp->place / P.n_slabs : tp->place;
+            if (DEEP) {
+                slab = tp->place - seg * P.n_slabs;
+                planes = min(kSupportW, pr.n_w - kSupportW * slab);
+            }
+            x_lo = seg * P.segment;
+            width = min(P.segment, pr.n_u - x_lo);
+            cell_bytes = (uint32_t)pr.n_w * 8u;
+            // the subgrid's output; rows past its end fall outside the resource
+            const int s = band / P.nby;
+            out = static_cast<char*>(pr.grid_out) + 8 * (int64_t)s * pr.cells_per_sub;
+            out_bytes = (uint32_t)(pr.cells_per_sub * 8);
+            row_out = (band - s * P.nby) * kOwnerBand;
+            accumulate = P.accumulate;
+        }
+        const int row0 = band % P.nby * kOwnerBand;
+        const __amdgpu_buffer_rsrc_t ro = make_rsrc(out, out_bytes);
         // of four staged columns, lane l stores 16 bytes of rows l / 8 and
         // l / 8 + 8: half l mod 2 of column l / 2 mod 4
         const int st_col = (lane >> 1) & 3, st_half = lane & 1;
-        const uint32_t lane_off = (uint32_t)((row0 + ly) * pr.n_u + x_lo + st_col) * cell_bytes +
-                                  (uint32_t)(slab * kSupportW * 8 + st_half * 16);
-        const uint32_t group_rows = (uint32_t)(8 * pr.n_u) * cell_bytes;
+        const uint32_t lane_off = (uint32_t)((row_out + ly) * n_u + (slice ? 0 : x_lo) + st_col) * cell_bytes +
+                                  (uint32_t)((slice ? 0 : slab * kSupportW * 8) + st_half * 16);
+        const uint32_t group_rows = (uint32_t)(8 * n_u) * cell_bytes;
 
         F32x4 acc[2][2];
 #pragma unroll
@@ -428,7 +459,7 @@ __global__ __launch_bounds__(kOwnerMaxWaves* kWave) void grid_owner_kernel(Owner
                             const uint32_t rows = g == 0 ? 0 : group_rows;
                             if constexpr (DEEP) {
                                 const bool p0 = 2 * st_half < planes, p1 = 2 * st_half + 1 < planes;
-                                if (P.accumulate) {
+                                if (accumulate) {
                                     const auto a = __builtin_amdgcn_raw_buffer_load_b64(ro, p0 ? off : kOutOfRange, rows, 0);
                                     const auto b = __builtin_amdgcn_raw_buffer_load_b64(ro, p1 ? off + 8u : kOutOfRange, rows, 0);
                                     v = make_float4(v.x + __uint_as_float(a[0]), v.y + __uint_as_float(a[1]),
@@ -437,7 +468,7 @@ __global__ __launch_bounds__(kOwnerMaxWaves* kWave) void grid_owner_kernel(Owner
                                 if (p0) __builtin_amdgcn_raw_buffer_store_b64(U32x2{__float_as_uint(v.x), __float_as_uint(v.y)}, ro, off, rows, 0);
                                 if (p1) __builtin_amdgcn_raw_buffer_store_b64(U32x2{__float_as_uint(v.z), __float_as_uint(v.w)}, ro, off + 8u, rows, 0);
                             } else {
-                                if (P.accumulate) {
+                                if (accumulate) {
                                     const auto a = __builtin_amdgcn_raw_buffer_load_b128(ro, off, rows, 0);
                                     v = make_float4(v.x + __uint_as_float(a[0]), v.y + __uint_as_float(a[1]),
                                                     v.z + __uint_as_float(a[2]), v.w + __uint_as_float(a[3]));
@@ -551,6 +582,65 @@ __global__ __launch_bounds__(kOwnerMaxWaves* kWave) void grid_owner_kernel(Owner
     // the last workgroup publishes the moved visibilities the record pass
     // counted, for the fix-up pass, and clears the count for the next call
     if (finish_launch(P.ctl, 0u)) atomicExch(&P.ctl->moved.v[1], atomicExch(&P.ctl->moved.v[0], 0u));
+}
+
+// Join pass: adds the slices of each split task, in their order (so the sums are
+// the same on every run), and writes the segment. A workgroup takes 64 consecutive
+// halves of cells (16 bytes) of a row; its wavefronts share the slices, and their
+// sums meet in LDS.
+constexpr int kJoinWaves = 8;
+constexpr int kJoinAhead = 8;   // loads in flight
+
+__global__ __launch_bounds__(kJoinWaves* kWave) void grid_join_kernel(OwnerParams P, int n_chunks) {
+    __shared__ float4 s_sum[kJoinWaves][kWave];
+    const Problem& pr = P.prob;
+    const int lane = lane_id(), wv = uniform((int)(threadIdx.x / kWave));
+    const int task = (int)(blockIdx.x / (uint32_t)n_chunks), chunk = (int)(blockIdx.x - (uint32_t)task * n_chunks);
+    const ConstOwnerTaskPtr tp = (ConstOwnerTaskPtr)uniform_u64((uint64_t)P.tasks) + task;
+    const int s = tp->band / P.nby, seg = tp->place / P.n_slabs, slab = tp->place - seg * P.n_slabs;
+    const int row0 = (tp->band - s * P.nby) * kOwnerBand, x_lo = seg * P.segment;
+    const int width = min(P.segment, pr.n_u - x_lo);
+    const int e = chunk * kWave + lane;   // of [kOwnerBand rows][width][2 halves]
+    const int row = e / (2 * width), col = (e - row * 2 * width) >> 1, half = e & 1;
+    const int k0 = (int)P.first_slice[task], n = (int)P.first_slice[task + 1] - k0;
+    const int k_end = k0 + (int)((int64_t)n * (wv + 1) / kJoinWaves);
+    float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int k = k0 + (int)((int64_t)n * wv / kJoinWaves); k < k_end; k += kJoinAhead) {
+        float4 v[kJoinAhead];
+#pragma unroll
+        for (int j = 0; j < kJoinAhead; ++j) {
+            const OwnerSlice* x = P.slices + min(k + j, k_end - 1);
+            const int c = x_lo + col - x->x_lo;
+            const bool in = k + j < k_end && row < kOwnerBand && c >= 0 && c < x->width;
+            const char* at = P.partials + (int64_t)x->column * (int64_t)kOwnerColumnBytes;
+            v[j] = in ? *reinterpret_cast<const float4*>(at + ((row * x->width + c) * 2 + half) * 16)
+                      : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+#pragma unroll
+        for (int j = 0; j < kJoinAhead; ++j) {
+            sum.x += v[j].x;
+            sum.y += v[j].y;
+            sum.z += v[j].z;
+            sum.w += v[j].w;
+        }
+    }
+    s_sum[wv][lane] = sum;
+    __syncthreads();
+    if (wv != 0 || row >= kOwnerBand || row0 + row >= pr.n_v) return;
+#pragma unroll
+    for (int k = 1; k < kJoinWaves; ++k) {
+        const float4 v = s_sum[k][lane];
+        sum.x += v.x;
+        sum.y += v.y;
+        sum.z += v.z;
+        sum.w += v.w;
+    }
+    const int plane = slab * kSupportW + 2 * half;
+    float2* to = static_cast<float2*>(pr.grid_out) + (int64_t)s * pr.cells_per_sub +
+                 ((int64_t)(row0 + row) * pr.n_u + x_lo + col) * pr.n_w + plane;
+    const float2 a = make_float2(sum.x, sum.y), b = make_float2(sum.z, sum.w);
+    if (plane < pr.n_w) to[0] = P.accumulate ? make_float2(to[0].x + a.x, to[0].y + a.y) : a;
+    if (plane + 1 < pr.n_w) to[1] = P.accumulate ? make_float2(to[1].x + b.x, to[1].y + b.y) : b;
 }
 
 // Record pass: lane by lane in input order, kRecordPerLane visibilities 64
@@ -750,12 +840,18 @@ hipError_t launch_owner_f(const OwnerParams& p, int blocks, int waves, size_t ma
 
 hipError_t launch_grid_owner(const OwnerParams& p, int gcf_kind, int n_cu, size_t max_lds, hipStream_t stream) {
     // one workgroup per CU, of as many wavefronts as there are tasks for them
-    const int waves = (int)std::min<int64_t>(kOwnerMaxWaves, std::max<int64_t>(1, (p.n_tasks + n_cu - 1) / n_cu));
-    const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>(n_cu, (p.n_tasks + waves - 1) / waves));
-    if (gcf_kind == kGcfF32) return launch_owner_f<kGcfF32>(p, blocks, waves, max_lds, stream);
-    if (gcf_kind == kGcfF16) return launch_owner_f<kGcfF16>(p, blocks, waves, max_lds, stream);
-    if (gcf_kind == kGcfBF16) return launch_owner_f<kGcfBF16>(p, blocks, waves, max_lds, stream);
-    return hipErrorInvalidValue;
+    const int64_t n_runs = p.n_tasks - p.n_split + p.n_slices;
+    const int waves = (int)std::min<int64_t>(kOwnerMaxWaves, std::max<int64_t>(1, (n_runs + n_cu - 1) / n_cu));
+    const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>(n_cu, (n_runs + waves - 1) / waves));
+    hipError_t e = hipErrorInvalidValue;
+    if (gcf_kind == kGcfF32) e = launch_owner_f<kGcfF32>(p, blocks, waves, max_lds, stream);
+    if (gcf_kind == kGcfF16) e = launch_owner_f<kGcfF16>(p, blocks, waves, max_lds, stream);
+    if (gcf_kind == kGcfBF16) e = launch_owner_f<kGcfBF16>(p, blocks, waves, max_lds, stream);
+    if (e != hipSuccess || p.n_split == 0) return e;
+    const int n_chunks = (kOwnerBand * p.segment * 2 + kWave - 1) / kWave;
+    hipLaunchKernelGGL(grid_join_kernel, dim3((unsigned)p.n_split * (unsigned)n_chunks), dim3(kJoinWaves * kWave), 0,
+                       stream, p, n_chunks);
+    return hipGetLastError();
 }
 
 hipError_t launch_grid_record(const Problem& pr, int64_t n_vis, const uint32_t* plan_start, const OwnerPlaces* place,

@@ -119,12 +119,11 @@ __device__ __forceinline__ int64_t lower_bound(const Key* keys, int64_t n, Key k
 
 // Task j before the sort by weight: segment and slab of a band. Sort key: the
 // complement of its weight (records, and its columns' stores), so that the
-// heaviest comes first. Thread 0 of the grid also finds the number of places.
+// heaviest comes first.
 template <class Key>
 __global__ void owner_tasks_kernel(OwnerShape h, const Key* keys, int64_t n_slots, Key n_keys, int64_t n_tasks,
-                                   OwnerTask* tasks, uint32_t* weights, uint32_t* idx, int64_t* n_items) {
+                                   OwnerTask* tasks, uint32_t* weights, uint32_t* idx) {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j == 0) *n_items = lower_bound(keys, n_slots, n_keys);
     if (j >= n_tasks) return;
     const int64_t per_band = (int64_t)h.n_seg * h.n_slabs;
     const int64_t band = j / per_band;
@@ -139,8 +138,104 @@ __global__ void owner_tasks_kernel(OwnerShape h, const Key* keys, int64_t n_slot
     idx[j] = (uint32_t)j;
 }
 
-__global__ void gather_tasks_kernel(const OwnerTask* tasks, const uint32_t* order, int64_t n_tasks, OwnerTask* out) {
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Sum of x over the threads before this one, and over all of them in *total. part
+// holds one entry per thread.
+__device__ __forceinline__ uint32_t sum_before(uint32_t x, uint32_t* part, uint32_t* total) {
+    const int t = (int)threadIdx.x, n = (int)blockDim.x;
+    __syncthreads();
+    part[t] = x;
+    __syncthreads();
+    for (int d = 1; d < n; d *= 2) {
+        const uint32_t y = t >= d ? part[t - d] : 0u;
+        __syncthreads();
+        part[t] += y;
+        __syncthreads();
+    }
+    *total = part[n - 1];
+    return part[t] - x;
+}
+
+constexpr int kTaskThreads = 256;
+
+// Slices of the tasks (j in order, heaviest first) that are longer than a slice
+// may be, where the tasks are uneven; one workgroup.
+template <class Key>
+__device__ void cut_tasks(const OwnerShape& h, const Key* keys, int64_t n_slots, Key n_keys, const OwnerTask* tasks,
+                          const uint32_t* weights, const uint32_t* order, int64_t n_tasks, int64_t room,
+                          OwnerSlice* slices, uint32_t* first_slice, OwnerCounts* counts) {
+    __shared__ uint32_t part[kTaskThreads];
+    const int64_t n_items = lower_bound(keys, n_slots, n_keys);
+    const int64_t work = n_items * h.n_slabs;
+    const int64_t share = max((work + kOwnerSlices - 1) / kOwnerSlices, (int64_t)kOwnerMinSlice);
+    const uint32_t longest = (uint32_t)((share + kWave - 1) / kWave * kWave);
+    // weights are complements and include the columns (at most h.segment)
+    const bool uneven = ~weights[0] > work / kOwnerEven + kOwnerJoin + h.segment;
+    int64_t n_split = uneven ? lower_bound(weights, n_tasks, ~(longest + (uint32_t)h.segment)) : 0;
+    auto length = [&](const OwnerTask& t) {   // of its slices: equal, whole batches of a wavefront
+        const uint32_t n = t.end - t.begin, k = (n + longest - 1) / longest;
+        return ((n + k - 1) / k + kWave - 1) / kWave * kWave;
+    };
+    uint32_t n_slices = 0;
+    for (int64_t r = 0; r < n_split; r += kTaskThreads) {
+        const int64_t j = r + threadIdx.x;
+        uint32_t k = 0, all = 0;
+        if (j < n_split) {
+            const OwnerTask t = tasks[order[j]];
+            const uint32_t len = length(t);
+            k = (t.end - t.begin + len - 1) / len;
+        }
+        const uint32_t before = n_slices + sum_before(k, part, &all);
+        if (j < n_split && j < room) first_slice[j] = before;
+        n_slices += all;
+    }
+    if (n_split > room || n_slices > room) n_split = n_slices = 0;   // (see kOwnerMaxSlices: there is room)
+    if (threadIdx.x == 0) first_slice[n_split] = n_slices;
+    __syncthreads();
+    uint32_t columns = 0;
+    for (uint32_t r = 0; r < n_slices; r += kTaskThreads) {
+        const uint32_t i = r + threadIdx.x;
+        OwnerSlice x{};
+        uint32_t all = 0;
+        if (i < n_slices) {
+            int64_t lo = 0, hi = n_split;   // first_slice[lo] <= i < first_slice[hi]
+            while (hi - lo > 1) {
+                const int64_t mid = (lo + hi) >> 1;
+                if (first_slice[mid] <= i) lo = mid; else hi = mid;
+            }
+            const OwnerTask t = tasks[order[lo]];
+            const uint32_t len = length(t);
+            x.begin = t.begin + (i - first_slice[lo]) * len;
+            x.end = min(t.end, x.begin + len);
+            x.band = t.band;
+            const int seg = t.place / h.n_slabs;
+            x.slab = t.place - seg * h.n_slabs;
+            const int x_lo = seg * h.segment, x_hi = min(x_lo + h.segment, h.n_u);
+            const Key base = (Key)((int64_t)t.band * h.n_u);
+            const int c0 = (int)(keys[x.begin] - base), c1 = (int)(keys[x.end - 1] - base);
+            x.x_lo = max(x_lo, c0 & ~7);
+            x.width = min(x_hi, c1 + kSupportUV) - x.x_lo;
+            x.task = (int32_t)lo;
+        }
+        x.column = columns + sum_before((uint32_t)x.width, part, &all);
+        if (i < n_slices) slices[i] = x;
+        columns += all;
+    }
+    if (threadIdx.x == 0) *counts = OwnerCounts{n_items, (int64_t)columns, (int32_t)n_split, (int32_t)n_slices};
+}
+
+// Workgroup 0 cuts the heavy tasks, the others bring all tasks into order.
+template <class Key>
+__global__ __launch_bounds__(kTaskThreads) void order_tasks_kernel(OwnerShape h, const Key* keys, int64_t n_slots,
+                                                                   Key n_keys, const OwnerTask* tasks,
+                                                                   const uint32_t* weights, const uint32_t* order,
+                                                                   int64_t n_tasks, int64_t room, OwnerTask* out,
+                                                                   OwnerSlice* slices, uint32_t* first_slice,
+                                                                   OwnerCounts* counts) {
+    if (blockIdx.x == 0) {
+        cut_tasks(h, keys, n_slots, n_keys, tasks, weights, order, n_tasks, room, slices, first_slice, counts);
+        return;
+    }
+    const int64_t r = (int64_t)(blockIdx.x - 1) * kTaskThreads + threadIdx.x;
     if (r < n_tasks) out[r] = tasks[order[r]];
 }
 
@@ -306,14 +401,15 @@ hipError_t sort_t(const Problem& pr, const int64_t* offsets, int64_t n_sub, int6
 
 template <class Key>
 hipError_t owner_t(const OwnerShape& h, const int64_t* offsets, const uint32_t* plan_start, OwnerPlaces* places,
-                   OwnerTask* tasks, int64_t* n_items, Key n_keys, int end_bit, DeviceTemp& temp, hipStream_t stream) {
+                   OwnerTask* tasks, OwnerSlice* slices, uint32_t* first_slice, OwnerCounts* counts, Key n_keys,
+                   int end_bit, DeviceTemp& temp, hipStream_t stream) {
     const int64_t n_slots = 2 * h.n_vis, n_tasks = h.tasks();
     size_t slot_sort = 0, task_sort = 0;
     hipError_t e = radix_bytes<Key>(n_slots, end_bit, stream, &slot_sort);
     if (e == hipSuccess) e = radix_bytes<uint32_t>(n_tasks, 32, stream, &task_sort);
     if (e != hipSuccess) return e;
     // keys and slots in and out, tasks with their weights and ranks in and
-    // out, the sorts' own storage, the item count
+    // out, the sorts' own storage, the counts
     const size_t kb = up256(sizeof(Key) * (size_t)n_slots), sb = up256(4 * (size_t)n_slots);
     const size_t tb = up256(sizeof(OwnerTask) * (size_t)n_tasks), wb = up256(4 * (size_t)n_tasks);
     const size_t own = up256(std::max(slot_sort, task_sort));
@@ -333,7 +429,7 @@ hipError_t owner_t(const OwnerShape& h, const int64_t* offsets, const uint32_t* 
     uint32_t* w[4];
     for (uint32_t*& x : w) x = reinterpret_cast<uint32_t*>(take(wb));
     char* sort_own = take(own);
-    int64_t* d_items = reinterpret_cast<int64_t*>(take(256));
+    OwnerCounts* d_counts = reinterpret_cast<OwnerCounts*>(take(256));
     hipLaunchKernelGGL((owner_keys_kernel<Key>), dim3(grid_of(h.n_vis)), dim3(256), 0, stream, h, offsets, plan_start,
                        n_keys, k_in, s_in);
     e = hipGetLastError();
@@ -344,17 +440,17 @@ hipError_t owner_t(const OwnerShape& h, const int64_t* offsets, const uint32_t* 
         hipLaunchKernelGGL((owner_places_kernel<Key>), dim3(grid_of(n_slots)), dim3(256), 0, stream, k_out, s_out,
                            n_slots, n_keys, reinterpret_cast<uint32_t*>(places));
         hipLaunchKernelGGL((owner_tasks_kernel<Key>), dim3(grid_of(n_tasks)), dim3(256), 0, stream, h, k_out, n_slots,
-                           n_keys, n_tasks, t_in, w[0], w[2], d_items);
+                           n_keys, n_tasks, t_in, w[0], w[2]);
         e = hipGetLastError();
     }
     if (e == hipSuccess)
         e = hipcub::DeviceRadixSort::SortPairs(sort_own, task_sort, w[0], w[1], w[2], w[3], n_tasks, 0, 32, stream);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(gather_tasks_kernel, dim3(grid_of(n_tasks)), dim3(256), 0, stream, t_in, w[3], n_tasks,
-                           tasks);
+        hipLaunchKernelGGL((order_tasks_kernel<Key>), dim3(grid_of(n_tasks) + 1), dim3(kTaskThreads), 0, stream, h, k_out,
+                           n_slots, n_keys, t_in, w[1], w[3], n_tasks, h.slices(), tasks, slices, first_slice, d_counts);
         e = hipGetLastError();
     }
-    if (e == hipSuccess) e = hipMemcpyAsync(n_items, d_items, sizeof(int64_t), hipMemcpyDeviceToHost, stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(counts, d_counts, sizeof(OwnerCounts), hipMemcpyDeviceToHost, stream);
     const hipError_t es = hipStreamSynchronize(stream);
     return e == hipSuccess ? es : e;
 }
@@ -376,15 +472,15 @@ hipError_t sort_visibilities(const Problem& pr, const int64_t* offsets_host, con
 }
 
 hipError_t build_owner_order(const OwnerShape& h, const int64_t* offsets, const uint32_t* plan_start,
-                             OwnerPlaces* places, OwnerTask* tasks, int64_t* n_items, DeviceTemp& temp,
-                             hipStream_t stream) {
+                             OwnerPlaces* places, OwnerTask* tasks, OwnerSlice* slices, uint32_t* first_slice,
+                             OwnerCounts* counts, DeviceTemp& temp, hipStream_t stream) {
     const int64_t n_keys = h.n_sub * h.nby * h.n_u;
     int end_bit = 1;
     while ((int64_t(1) << end_bit) <= n_keys) ++end_bit;
-    return end_bit <= 32 ? owner_t<uint32_t>(h, offsets, plan_start, places, tasks, n_items, (uint32_t)n_keys, end_bit,
-                                             temp, stream)
-                         : owner_t<uint64_t>(h, offsets, plan_start, places, tasks, n_items, (uint64_t)n_keys, end_bit,
-                                             temp, stream);
+    return end_bit <= 32 ? owner_t<uint32_t>(h, offsets, plan_start, places, tasks, slices, first_slice, counts,
+                                             (uint32_t)n_keys, end_bit, temp, stream)
+                         : owner_t<uint64_t>(h, offsets, plan_start, places, tasks, slices, first_slice, counts,
+                                             (uint64_t)n_keys, end_bit, temp, stream);
 }
 
 hipError_t launch_count_tiles(const FitChunk* chunks, int64_t n_chunks, const uint32_t* start, const FitRule& rule,
