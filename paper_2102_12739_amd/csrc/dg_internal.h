@@ -92,7 +92,11 @@ struct LaunchParams {
 // window reaches.
 constexpr int kOwnerBand = 16;            // rows of a band
 constexpr int kOwnerMaxSegment = 112;     // columns of a segment, at most
-constexpr int kOwnerMaxPlanes = 16384;    // w planes of a subgrid that a record can name
+// w planes of a subgrid, at most: every slab's task walks all visibilities of its
+// band and segment, so deeper stacks scatter instead (400 000 visibilities on 128 x
+// 128: 512 planes 1259 us, scattered 5089; 1536 planes 3878 and 5180; 3000 planes
+// 6625 and 5437; 20 000 on 32 x 32: 1536 planes 461 and 563; 2000 planes 717 and 566).
+constexpr int kOwnerMaxPlanes = 1600;
 constexpr uint32_t kNoPlace = 0xFFFFFFFFu;
 
 struct OwnerPlaces {
