@@ -216,7 +216,7 @@ struct dg_plan_ {
     uint64_t version = 0;         // bumped when tiles or work order change
     // owner-computes adjoint (built by degrid_plan_sort)
     void* own_lists = nullptr;          // the five below, in one allocation
-    OwnerPlaces* d_places = nullptr;    // positions in the owner order per visibility
+    OwnerPlaces* d_places = nullptr;    // positions in the owner order per visibility (own.direct: the inverse)
     OwnerTask* d_tasks = nullptr;
     OwnerSlice* d_slices = nullptr;     // of the heavy tasks
     uint32_t* d_first_slice = nullptr;
@@ -618,6 +618,7 @@ dg_status build_order(dg_plan_* p, const double* uvw, bool gridding, hipStream_t
     h.n_slabs = (d.n_w + kSupportW - 1) / kSupportW;
     h.segment = owner_segment(p->n_sub * h.nby * h.n_slabs, d.n_u, p->n_cu);
     h.n_seg = (d.n_u + h.segment - 1) / h.segment;
+    h.direct = h.n_vis <= kOwnerDirect;
     // too deep, or outside what its positions and tasks can name: the adjoint scatters
     if (d.n_w > kOwnerMaxPlanes || h.n_vis > 0x7FFFFFFF || h.tasks() > 0x7FFFFFFF) {
         e = hipStreamSynchronize(stream);
@@ -638,10 +639,11 @@ dg_status build_order(dg_plan_* p, const double* uvw, bool gridding, hipStream_t
         e = build_owner_order(h, p->d_offsets, p->d_plan_start, p->d_places, p->d_tasks, p->d_slices, p->d_first_slice,
                               &p->own_counts, temp, stream);
     if (e != hipSuccess) return hip_fail(e, "ordering the adjoint");
-    const size_t rb = std::max<size_t>(1, (size_t)p->own_counts.n_items) * sizeof(OwnerRecord);
-    e = hipMalloc(&p->own_space, rb + (size_t)p->own_counts.columns * kOwnerColumnBytes);
+    const size_t rb = h.direct ? 0 : std::max<size_t>(1, (size_t)p->own_counts.n_items) * sizeof(OwnerRecord);
+    const size_t cb = (size_t)p->own_counts.columns * kOwnerColumnBytes;
+    if (rb + cb > 0) e = hipMalloc(&p->own_space, rb + cb);
     if (e != hipSuccess) { p->own_space = nullptr; return hip_fail(e, "hipMalloc(gridding workspace)"); }
-    p->d_records = static_cast<OwnerRecord*>(p->own_space);
+    p->d_records = h.direct ? nullptr : static_cast<OwnerRecord*>(p->own_space);
     p->d_partials = static_cast<char*>(p->own_space) + rb;
     p->own_tasks = h.tasks();
     return DG_OK;
@@ -800,13 +802,15 @@ dg_status grid_adjoint(dg_plan p, const void* vis, const void* g_uv, const void*
     if (!subgrids_out && p->n_sub > 0) return fail(DG_ERR_INVALID_ARG, "subgrids_out is NULL");
     const int64_t out_bytes = p->n_sub * (int64_t)p->desc.n_v * p->desc.n_u * p->desc.n_w * 8;
     if (p->own_tasks > 0) {
-        // owner-computes: the records, every output cell written once, the fix-up
+        // owner-computes: the records (not for small plans), every output cell written once, the fix-up
         if (!vis || !g_uv || !g_w || !uvw) return fail(DG_ERR_INVALID_ARG, "a device pointer is NULL");
         if (dg_status s = check_alignment(p->desc, nullptr, g_uv, g_w, uvw, vis, nullptr, subgrids_out); s != DG_OK)
             return s;
         OwnerParams op{};
         op.prob = problem_of(p, nullptr, g_uv, g_w, uvw, const_cast<void*>(vis), subgrids_out);
         op.records = p->d_records;
+        op.items = reinterpret_cast<const uint32_t*>(p->d_places);
+        op.plan_start = p->d_plan_start;
         op.tasks = p->d_tasks;
         op.slices = p->d_slices;
         op.first_slice = p->d_first_slice;
@@ -821,13 +825,16 @@ dg_status grid_adjoint(dg_plan p, const void* vis, const void* g_uv, const void*
         op.n_slabs = p->own.n_slabs;
         const int64_t n = p->offsets.back();
         const int max_blocks = std::max(1, 2 * p->n_cu);
-        hipError_t e = launch_grid_record(op.prob, n, p->d_plan_start, p->d_places, p->d_records, p->ds.ctl,
-                                          p->d_own_ctl, max_blocks, stream);
+        hipError_t e = hipSuccess;
+        if (!p->own.direct)
+            e = launch_grid_record(op.prob, n, p->d_plan_start, p->d_places, p->d_records, p->ds.ctl, p->d_own_ctl,
+                                   max_blocks, stream);
         if (e == hipSuccess)
             e = launch_grid_owner(op, p->desc.gcf_dtype, p->n_cu, p->max_lds, stream);
         if (e == hipSuccess)
-            e = launch_grid_fixup(op.prob, p->d_offsets, p->n_sub, n, p->d_plan_start, p->d_own_ctl,
-                                  p->desc.gcf_dtype, max_blocks, stream);
+            e = launch_grid_fixup(op.prob, p->d_offsets, p->n_sub, n, p->d_plan_start,
+                                  p->own.direct ? nullptr : p->d_own_ctl, p->ds.ctl, p->desc.gcf_dtype, max_blocks,
+                                  stream);
         if (e != hipSuccess) return hip_fail(e, "adjoint kernel launch");
         p->last_stream = stream;
         p->launched = true;

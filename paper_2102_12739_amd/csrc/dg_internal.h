@@ -160,9 +160,19 @@ struct OwnerCounts {
     int32_t n_slices;
 };
 
+// Plans of at most this many visibilities have no records: the owner pass reads the
+// visibilities themselves, and the fix-up pass checks every one. That is one launch
+// less, on the host too, and more scattered reads (records and direct): 2 subgrids
+// with 8000 visibilities 20.7 and 14.8 us, 16 with 32 000 36.8 and 33.2, with
+// 128 000 47.9 and 45.0, with 512 000 88.3 and 95.5; 12 planes, 4 subgrids with
+// 32 000 50.9 and 49.5, with 128 000 79.9 and 80.4, with 256 000 112 and 118.
+constexpr int64_t kOwnerDirect = 1 << 17;
+
 struct OwnerParams {
-    Problem prob;                  // g_uv, g_w, vis (input), grid_out
-    const OwnerRecord* records;    // from the record pass
+    Problem prob;                  // g_uv, g_w, vis (input), grid_out; uvw without records
+    const OwnerRecord* records;    // from the record pass, or nullptr: the two below
+    const uint32_t* items;         // visibility at each position of the owner order
+    const uint32_t* plan_start;    // first tap of each visibility at the sort
     const OwnerTask* tasks;        // heaviest first, n_split of them in slices
     const OwnerSlice* slices;      // by task and position
     const uint32_t* first_slice;   // per split task, and the end
@@ -219,10 +229,11 @@ hipError_t launch_grid_owner(const OwnerParams& p, int gcf_kind, int n_cu, size_
 hipError_t launch_grid_record(const Problem& pr, int64_t n_vis, const uint32_t* plan_start, const OwnerPlaces* place,
                               OwnerRecord* records, Ctl* ctl, Ctl* own_ctl, int max_blocks, hipStream_t stream);
 // Adds, with atomics, the visibilities whose first tap differs from the
-// plan's; nothing when the record pass counted none. n_vis visibilities of one
-// problem; vis_offsets on the device.
+// plan's; nothing when the record pass counted none (own_ctl; nullptr: there was
+// none, and every visibility is checked and the out-of-range count goes to ctl).
+// n_vis visibilities of one problem; vis_offsets on the device.
 hipError_t launch_grid_fixup(const Problem& pr, const int64_t* vis_offsets, int64_t n_sub, int64_t n_vis,
-                             const uint32_t* plan_start, const Ctl* own_ctl, int gcf_kind, int max_blocks,
+                             const uint32_t* plan_start, const Ctl* own_ctl, Ctl* ctl, int gcf_kind, int max_blocks,
                              hipStream_t stream);
 // tile_vis[t * kMaxNb + j] = visibility index of item j of tile t: through
 // perms[tile.problem] (a work-order permutation, or nullptr for input order)
@@ -287,10 +298,12 @@ hipError_t sort_visibilities(const Problem& pr, const int64_t* offsets_host, con
 // The owner order of the adjoint and its tasks, from the first taps: places
 // [n_vis] and tasks[shape.tasks()], heaviest first; the slices [shape.slices()]
 // of the heavy ones and first_slice [shape.slices() + 1]. *counts receives what
-// there is of them. Uses 'temp'; synchronises 'stream'.
+// there is of them. shape.direct: 'places' receives the visibility at each position
+// instead ([2 n_vis] uint32). Uses 'temp'; synchronises 'stream'.
 struct OwnerShape {
     int64_t n_sub, n_vis;
     int32_t nby, n_u, segment, n_seg, n_slabs;
+    bool direct;   // no records (kOwnerDirect)
     int64_t tasks() const { return n_sub * nby * n_seg * n_slabs; }
     // room for slices (a visibility has two places, each reaches two segments)
     int64_t slices() const { return std::min<int64_t>(kOwnerMaxSlices, 8 * n_vis * n_slabs / kOwnerMinSlice + 1); }

@@ -4,6 +4,7 @@
 #include "dg_device.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace dg {
 namespace {
@@ -170,7 +171,8 @@ __global__ __launch_bounds__(kBlockThreads) void grid_adjoint_kernel(LaunchParam
 // Owner-computes adjoint
 // ---------------------------------------------------------------------------
 //
-// Three launches, or four. The record pass reads the visibilities in input order and
+// Three launches, or four; on small plans two, or three. The record pass (not on
+// small plans: kOwnerDirect) reads the visibilities in input order and
 // writes what the sums need of each (first tap, table rows, value: 16 bytes)
 // at its places in the owner order. The owner pass sums and writes every
 // output cell once with plain stores: no global atomics, and the sums do not
@@ -313,7 +315,29 @@ __device__ __forceinline__ void owner_item(F32x4 (&acc)[2][2], float c0, float c
     }
 }
 
-template <int F, bool LDS_TAB, bool DEEP>
+// What the sums need of a visibility at coordinates (u, v, w), or a record that is
+// skipped where it is out of range or starts elsewhere than at the sort.
+__device__ __forceinline__ uint4 owner_record(const Problem& pr, double u, double v, double w, uint32_t plan_start,
+                                              float2 vis, bool& in_range, bool& moved) {
+    int32_t cell = 0, tab = 0, ow = 0, x0 = 0, y0 = 0;
+    in_range = coords_from(pr, u, v, w, cell, tab, ow, x0, y0);
+    const uint32_t f = ((uint32_t)y0 << 16) | (uint32_t)x0;
+    moved = in_range && f != plan_start;
+    const uint32_t z0 = (uint32_t)(cell - (y0 * pr.n_u + x0) * pr.n_w);
+    return make_uint4(in_range && !moved ? f : kNoStart,
+                      (uint32_t)(tab / (kSupportUV * kSupportUV)) | ((uint32_t)ow << kRecBlockBits) | (z0 << kRecPlaneShift),
+                      __float_as_uint(vis.x), __float_as_uint(vis.y));
+}
+
+// One visibility's inputs, in flight.
+struct OwnerInputs {
+    double u, v, w;
+    float2 vis;
+    uint32_t plan_start;
+};
+
+// DIRECT: no records; the visibilities are read through P.items.
+template <int F, bool LDS_TAB, bool DEEP, bool DIRECT>
 __global__ __launch_bounds__(kOwnerMaxWaves* kWave) void grid_owner_kernel(OwnerParams P) {
     extern __shared__ __attribute__((aligned(16))) char s_mem[];
     const int lane = lane_id();
@@ -484,14 +508,26 @@ __global__ __launch_bounds__(kOwnerMaxWaves* kWave) void grid_owner_kernel(Owner
         };
 
         auto fetch = [&](uint32_t pos) {
-            const uint32_t p = pos + (uint32_t)lane;
-            return reinterpret_cast<const uint4*>(P.records)[p < end ? p : end - 1];
+            const uint32_t p = min(pos + (uint32_t)lane, end - 1);
+            if constexpr (DIRECT) {
+                const int64_t i = P.items[p];
+                const double* c = pr.uvw + 3 * i;
+                return OwnerInputs{c[0], c[1], c[2], static_cast<const float2*>(pr.vis)[i], P.plan_start[i]};
+            } else {
+                return reinterpret_cast<const uint4*>(P.records)[p];
+            }
         };
-        uint4 nxt = make_uint4(kNoStart, 0u, 0u, 0u);
+        decltype(fetch(0)) nxt{};
         if (begin < end) nxt = fetch(begin);
         for (uint32_t pos = begin; pos < end; pos += kWave) {
             // Lane j prepares record j; the next 64 are requested before.
-            const uint4 x = nxt;
+            uint4 x;
+            if constexpr (DIRECT) {
+                bool in_range, moved;
+                x = owner_record(pr, nxt.u, nxt.v, nxt.w, nxt.plan_start, nxt.vis, in_range, moved);
+            } else {
+                x = nxt;
+            }
             const int n = (int)min((uint32_t)kWave, end - pos);
             if (pos + kWave < end) nxt = fetch(pos + kWave);
             int flags = 0, at = 0, dz = 0;
@@ -581,7 +617,7 @@ __global__ __launch_bounds__(kOwnerMaxWaves* kWave) void grid_owner_kernel(Owner
     }
     // the last workgroup publishes the moved visibilities the record pass
     // counted, for the fix-up pass, and clears the count for the next call
-    if (finish_launch(P.ctl, 0u)) atomicExch(&P.ctl->moved.v[1], atomicExch(&P.ctl->moved.v[0], 0u));
+    if (!DIRECT && finish_launch(P.ctl, 0u)) atomicExch(&P.ctl->moved.v[1], atomicExch(&P.ctl->moved.v[0], 0u));
 }
 
 // Join pass: adds the slices of each split task, in their order (so the sums are
@@ -680,17 +716,9 @@ __global__ __launch_bounds__(kBlockThreads) void grid_record_kernel(Problem pr, 
 #pragma unroll
         for (int k = 0; k < kRecordPerLane; ++k) {
             const int64_t i = w0 + k * kWave + lane;
-            int32_t cell = 0, tab = 0, ow = 0, x0 = 0, y0 = 0;
             bool in_range = false, moved = false;
             if (i < n_vis) {
-                in_range = coords_from(pr, cu[k], cv[k], cw[k], cell, tab, ow, x0, y0);
-                const uint32_t f = ((uint32_t)y0 << 16) | (uint32_t)x0;
-                moved = in_range && f != ps[k];
-                const uint32_t z0 = (uint32_t)(cell - (y0 * pr.n_u + x0) * pr.n_w);
-                const uint4 r = make_uint4(in_range && !moved ? f : kNoStart,
-                                           (uint32_t)(tab / (kSupportUV * kSupportUV)) |
-                                               ((uint32_t)ow << kRecBlockBits) | (z0 << kRecPlaneShift),
-                                           __float_as_uint(vv[k].x), __float_as_uint(vv[k].y));
+                const uint4 r = owner_record(pr, cu[k], cv[k], cw[k], ps[k], vv[k], in_range, moved);
                 if (at[k].x != kNoPlace) records[at[k].x] = r;
                 if (at[k].y != kNoPlace) records[at[k].y] = r;
             }
@@ -704,12 +732,14 @@ __global__ __launch_bounds__(kBlockThreads) void grid_record_kernel(Problem pr, 
 
 // Visibilities the owner pass skipped (first tap differs from the plan's),
 // added with atomics by whole wavefronts. Ends at once when the record pass
-// found none.
-template <int F>
+// found none. CHECK: without a record pass, so it counts those out of range too.
+template <int F, bool CHECK>
 __global__ __launch_bounds__(kBlockThreads) void grid_fixup_kernel(Problem pr, const int64_t* offsets,
                                                                    int64_t n_sub, int64_t n_vis,
-                                                                   const uint32_t* plan_start, const Ctl* own_ctl) {
-    if (own_ctl->moved.v[1] == 0u) return;
+                                                                   const uint32_t* plan_start, const Ctl* own_ctl,
+                                                                   Ctl* ctl) {
+    if (!CHECK && own_ctl->moved.v[1] == 0u) return;
+    uint32_t wave_oob = 0;
     const int lane = lane_id();
     const int tv = lane >> 3, tu = lane & 7;
     const int64_t lane_cell = (int64_t)(tv * pr.n_u + tu) * pr.n_w;
@@ -718,10 +748,12 @@ __global__ __launch_bounds__(kBlockThreads) void grid_fixup_kernel(Problem pr, c
     for (int64_t w0 = first * kWave; w0 < n_vis; w0 += n_waves * kWave) {
         const int64_t i = w0 + lane;
         int32_t cell = 0, tab = 0, ow = 0, x0 = 0, y0 = 0;
-        bool redo = false;
-        if (i < n_vis)
-            redo = vis_coords(pr, i, cell, tab, ow, x0, y0) &&
-                   (((uint32_t)y0 << 16) | (uint32_t)x0) != plan_start[i];
+        bool in_range = false, redo = false;
+        if (i < n_vis) {
+            in_range = vis_coords(pr, i, cell, tab, ow, x0, y0);
+            redo = in_range && (((uint32_t)y0 << 16) | (uint32_t)x0) != plan_start[i];
+        }
+        if (CHECK) wave_oob += (uint32_t)__popcll(__ballot(i < n_vis && !in_range));
         uint64_t mask = __ballot(redo);
         if (mask == 0) continue;
         // subgrid of each visibility to redo
@@ -758,6 +790,7 @@ __global__ __launch_bounds__(kBlockThreads) void grid_fixup_kernel(Problem pr, c
                 unsafeAtomicAdd(dst + q, g * __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c[q]), j)));
         }
     }
+    if (CHECK) finish_launch<true>(ctl, wave_oob);
 }
 
 }  // namespace
@@ -820,12 +853,12 @@ hipError_t adjoint_kernel_occupancy(int gcf_kind, int variant, int* n) {
     return hipErrorInvalidValue;
 }
 
-template <int F, bool LDS_TAB>
+template <int F, bool LDS_TAB, bool DIRECT>
 hipError_t launch_owner_t(const OwnerParams& p, int blocks, int waves, size_t lds, hipStream_t s) {
     if (p.n_slabs > 1)
-        hipLaunchKernelGGL((grid_owner_kernel<F, LDS_TAB, true>), dim3(blocks), dim3(waves * kWave), lds, s, p);
+        hipLaunchKernelGGL((grid_owner_kernel<F, LDS_TAB, true, DIRECT>), dim3(blocks), dim3(waves * kWave), lds, s, p);
     else
-        hipLaunchKernelGGL((grid_owner_kernel<F, LDS_TAB, false>), dim3(blocks), dim3(waves * kWave), lds, s, p);
+        hipLaunchKernelGGL((grid_owner_kernel<F, LDS_TAB, false, DIRECT>), dim3(blocks), dim3(waves * kWave), lds, s, p);
     return hipGetLastError();
 }
 
@@ -834,8 +867,12 @@ hipError_t launch_owner_f(const OwnerParams& p, int blocks, int waves, size_t ma
     // the whole table in LDS where it fits beside the wavefronts' own areas
     const size_t own = (size_t)waves * kOwnerWaveBytes + (size_t)p.prob.os_w * sizeof(float4);
     const size_t with_table = own + p.prob.guv_bytes + kOwnerTablePad * GcfTraits<F>::kBytes;
-    return with_table + kOwnerStaticLds <= max_lds ? launch_owner_t<F, true>(p, blocks, waves, with_table, s)
-                                                   : launch_owner_t<F, false>(p, blocks, waves, own, s);
+    const bool lds_tab = with_table + kOwnerStaticLds <= max_lds;
+    if (!p.records)
+        return lds_tab ? launch_owner_t<F, true, true>(p, blocks, waves, with_table, s)
+                       : launch_owner_t<F, false, true>(p, blocks, waves, own, s);
+    return lds_tab ? launch_owner_t<F, true, false>(p, blocks, waves, with_table, s)
+                   : launch_owner_t<F, false, false>(p, blocks, waves, own, s);
 }
 
 hipError_t launch_grid_owner(const OwnerParams& p, int gcf_kind, int n_cu, size_t max_lds, hipStream_t stream) {
@@ -864,22 +901,29 @@ hipError_t launch_grid_record(const Problem& pr, int64_t n_vis, const uint32_t* 
     return hipGetLastError();
 }
 
-hipError_t launch_grid_fixup(const Problem& pr, const int64_t* vis_offsets, int64_t n_sub, int64_t n_vis,
-                             const uint32_t* plan_start, const Ctl* own_ctl, int gcf_kind, int max_blocks,
-                             hipStream_t stream) {
-    const dim3 blocks((unsigned)std::max<int64_t>(1, std::min<int64_t>((n_vis + kBlockThreads - 1) / kBlockThreads, max_blocks)));
-    if (gcf_kind == kGcfF32)
-        hipLaunchKernelGGL((grid_fixup_kernel<kGcfF32>), blocks, dim3(kBlockThreads), 0, stream, pr, vis_offsets,
-                           n_sub, n_vis, plan_start, own_ctl);
-    else if (gcf_kind == kGcfF16)
-        hipLaunchKernelGGL((grid_fixup_kernel<kGcfF16>), blocks, dim3(kBlockThreads), 0, stream, pr, vis_offsets,
-                           n_sub, n_vis, plan_start, own_ctl);
-    else if (gcf_kind == kGcfBF16)
-        hipLaunchKernelGGL((grid_fixup_kernel<kGcfBF16>), blocks, dim3(kBlockThreads), 0, stream, pr, vis_offsets,
-                           n_sub, n_vis, plan_start, own_ctl);
+template <int F>
+hipError_t launch_fixup_f(const Problem& pr, const int64_t* vis_offsets, int64_t n_sub, int64_t n_vis,
+                          const uint32_t* plan_start, const Ctl* own_ctl, Ctl* ctl, int blocks, hipStream_t s) {
+    if (own_ctl)
+        hipLaunchKernelGGL((grid_fixup_kernel<F, false>), dim3(blocks), dim3(kBlockThreads), 0, s, pr, vis_offsets, n_sub,
+                           n_vis, plan_start, own_ctl, ctl);
     else
-        return hipErrorInvalidValue;
+        hipLaunchKernelGGL((grid_fixup_kernel<F, true>), dim3(blocks), dim3(kBlockThreads), 0, s, pr, vis_offsets, n_sub,
+                           n_vis, plan_start, own_ctl, ctl);
     return hipGetLastError();
+}
+
+hipError_t launch_grid_fixup(const Problem& pr, const int64_t* vis_offsets, int64_t n_sub, int64_t n_vis,
+                             const uint32_t* plan_start, const Ctl* own_ctl, Ctl* ctl, int gcf_kind, int max_blocks,
+                             hipStream_t stream) {
+    const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>((n_vis + kBlockThreads - 1) / kBlockThreads, max_blocks));
+    auto launch = [&](auto f) {
+        return launch_fixup_f<decltype(f)::value>(pr, vis_offsets, n_sub, n_vis, plan_start, own_ctl, ctl, blocks, stream);
+    };
+    if (gcf_kind == kGcfF32) return launch(std::integral_constant<int, kGcfF32>{});
+    if (gcf_kind == kGcfF16) return launch(std::integral_constant<int, kGcfF16>{});
+    if (gcf_kind == kGcfBF16) return launch(std::integral_constant<int, kGcfBF16>{});
+    return hipErrorInvalidValue;
 }
 
 }  // namespace dg

@@ -106,6 +106,12 @@ __global__ void owner_places_kernel(const Key* keys, const uint32_t* slots, int6
     if (p < n_slots) places[slots[p]] = keys[p] < n_keys ? (uint32_t)p : kNoPlace;
 }
 
+// (Positions past the last place hold visibilities too; no task names them.)
+__global__ void owner_items_kernel(const uint32_t* slots, int64_t n_slots, uint32_t* items) {
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p < n_slots) items[p] = slots[p] >> 1;
+}
+
 // First position whose key is at least 'key'.
 template <class Key>
 __device__ __forceinline__ int64_t lower_bound(const Key* keys, int64_t n, Key key) {
@@ -437,8 +443,12 @@ hipError_t owner_t(const OwnerShape& h, const int64_t* offsets, const uint32_t* 
         e = hipcub::DeviceRadixSort::SortPairs(sort_own, slot_sort, k_in, k_out, s_in, s_out, n_slots, 0, end_bit,
                                                stream);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL((owner_places_kernel<Key>), dim3(grid_of(n_slots)), dim3(256), 0, stream, k_out, s_out,
-                           n_slots, n_keys, reinterpret_cast<uint32_t*>(places));
+        if (h.direct)
+            hipLaunchKernelGGL(owner_items_kernel, dim3(grid_of(n_slots)), dim3(256), 0, stream, s_out, n_slots,
+                               reinterpret_cast<uint32_t*>(places));
+        else
+            hipLaunchKernelGGL((owner_places_kernel<Key>), dim3(grid_of(n_slots)), dim3(256), 0, stream, k_out, s_out,
+                               n_slots, n_keys, reinterpret_cast<uint32_t*>(places));
         hipLaunchKernelGGL((owner_tasks_kernel<Key>), dim3(grid_of(n_tasks)), dim3(256), 0, stream, h, k_out, n_slots,
                            n_keys, n_tasks, t_in, w[0], w[2]);
         e = hipGetLastError();
