@@ -273,8 +273,11 @@ dg_status degrid_oob_count(dg_plan p, int64_t* count);
  * Every output stays in input order and every result is unchanged (each
  * visibility's sum does not depend on the order); only speed depends on uvw
  * matching the coordinates passed to later calls. Allocates the plan's
- * orders and the adjoint's workspace (about 45 bytes per visibility) and
- * temporary sort buffers; synchronises 'stream'. DG_ERR_UNSUPPORTED if N >= 2^32.
+ * orders and the adjoint's workspace (about 45 bytes per visibility; 20 up to
+ * 2^17 visibilities, more for the columns where they crowd) and temporary sort
+ * buffers. Where the device has no memory for the adjoint's part, the call
+ * succeeds as degrid_plan_sort_forward does. Synchronises 'stream'.
+ * DG_ERR_UNSUPPORTED if N >= 2^32.
  * Batches built from this plan before the call must be rebuilt.
  */
 dg_status degrid_plan_sort(dg_plan p, const double* uvw, hipStream_t stream);

@@ -624,10 +624,18 @@ dg_status build_order(dg_plan_* p, const double* uvw, bool gridding, hipStream_t
         e = hipStreamSynchronize(stream);
         return e == hipSuccess ? DG_OK : hip_fail(e, "sorting the work order");
     }
+    // without memory for it the work order stays by itself, and the adjoint scatters
+    auto without = [&](hipError_t why, const char* what) -> dg_status {
+        (void)hipStreamSynchronize(stream);
+        free_owner(p);
+        if (why != hipErrorOutOfMemory) return hip_fail(why, what);
+        (void)hipGetLastError();
+        return DG_OK;
+    };
     const size_t tb = (size_t)h.tasks() * sizeof(OwnerTask), pb = n * sizeof(OwnerPlaces);
     const size_t sb = (size_t)h.slices() * sizeof(OwnerSlice), fb = (size_t)(h.slices() + 1) * sizeof(uint32_t);
-    e = hipMalloc(&p->own_lists, sizeof(Ctl) + tb + sb + pb + fb);
-    if (e != hipSuccess) { p->own_lists = nullptr; return hip_fail(e, "hipMalloc(gridding order)"); }
+    e = fault_injected("gridding") ? hipErrorOutOfMemory : hipMalloc(&p->own_lists, sizeof(Ctl) + tb + sb + pb + fb);
+    if (e != hipSuccess) { p->own_lists = nullptr; return without(e, "hipMalloc(gridding order)"); }
     char* at = static_cast<char*>(p->own_lists);
     p->d_own_ctl = reinterpret_cast<Ctl*>(at);
     p->d_tasks = reinterpret_cast<OwnerTask*>(at + sizeof(Ctl));
@@ -638,11 +646,12 @@ dg_status build_order(dg_plan_* p, const double* uvw, bool gridding, hipStream_t
     if (e == hipSuccess)
         e = build_owner_order(h, p->d_offsets, p->d_plan_start, p->d_places, p->d_tasks, p->d_slices, p->d_first_slice,
                               &p->own_counts, temp, stream);
-    if (e != hipSuccess) return hip_fail(e, "ordering the adjoint");
+    if (e != hipSuccess) return without(e, "ordering the adjoint");
     const size_t rb = h.direct ? 0 : std::max<size_t>(1, (size_t)p->own_counts.n_items) * sizeof(OwnerRecord);
     const size_t cb = (size_t)p->own_counts.columns * kOwnerColumnBytes;
-    if (rb + cb > 0) e = hipMalloc(&p->own_space, rb + cb);
-    if (e != hipSuccess) { p->own_space = nullptr; return hip_fail(e, "hipMalloc(gridding workspace)"); }
+    if (fault_injected("gridding workspace")) e = hipErrorOutOfMemory;
+    else if (rb + cb > 0) e = hipMalloc(&p->own_space, rb + cb);
+    if (e != hipSuccess) { p->own_space = nullptr; return without(e, "hipMalloc(gridding workspace)"); }
     p->d_records = h.direct ? nullptr : static_cast<OwnerRecord*>(p->own_space);
     p->d_partials = static_cast<char*>(p->own_space) + rb;
     p->own_tasks = h.tasks();
