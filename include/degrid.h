@@ -179,8 +179,8 @@ dg_status degrid_execute(dg_plan p, const void* subgrids, const void* g_uv, cons
  *   subgrids, g_uv, g_w, uvw, vis_out  device arrays as for degrid_execute.
  *   oob_count    device int64, or NULL: receives this call's out-of-range
  *                count (written by the call's kernels, stream-ordered).
- * The scratch (a control block, the offsets and per-subgrid tile offsets:
- * 200 704 bytes) is one static device array per GPU, held until the
+ * The scratch (control blocks, the offsets and per-subgrid tile offsets:
+ * 235 776 bytes) is one static device array per GPU, held until the
  * process ends and shared by every call on that GPU: calls that overlap on
  * one GPU (two streams, or two host threads) race and give wrong results.
  * Calls no hipMalloc or hipFree. Every visibility's result equals

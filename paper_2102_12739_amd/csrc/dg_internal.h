@@ -331,14 +331,14 @@ void table_grad_shape(int os_uv, int os_w, bool want_uv, bool want_w, size_t max
 hipError_t launch_zero_f32(float* p, int64_t n, hipStream_t stream);
 
 // Degridding without a plan (defined in noalloc.hip): its scratch is a
-// file-scope device array of kNoAllocBytes per GPU (a control block, the
+// file-scope device array of kNoAllocBytes per GPU (control blocks, the
 // staged offsets and the tile offsets of at most kNoAllocMaxSubgrids
 // subgrids). Input-order tiles of nb visibilities; n_tiles = sum over
 // subgrids of ceil(N_s / nb). offsets_host [n_sub + 1] is copied into the
 // scratch on 'stream', or travels with the launch. oob_out (device, may be null) receives the launch's
 // out-of-range count. Allocates nothing.
 constexpr int64_t kNoAllocMaxSubgrids = 16384;
-constexpr size_t kNoAllocBytes = 200704;
+constexpr size_t kNoAllocBytes = 235776;
 // Resident workgroups of the kernel that call would launch on the current device.
 hipError_t noalloc_resident(int grid_kind, int gcf_kind, int* resident);
 hipError_t launch_degrid_noalloc(const Problem& pr, int grid_kind, int gcf_kind,

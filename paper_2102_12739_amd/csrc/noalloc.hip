@@ -4,8 +4,10 @@
 //
 // The scratch is one file-scope device array per GPU, `scratch`, of
 // kNoAllocBytes bytes, holding
-//   - a control block (the out-of-range count; the last workgroup of a launch
-//     leaves it cleared for the next);
+//   - control blocks (the out-of-range count; the last workgroup of a launch
+//     leaves its own cleared for the next). Calls that ask for the count take
+//     them in turn: two that overlap in one would miscount their workgroups'
+//     ends, and, with grids of two sizes, leave it so for every later call;
 //   - for calls of more than kArgSubgrids subgrids, the caller's visibility
 //     offsets, staged from the host ([S+1] int64), and the first tile of every
 //     subgrid ([S+1] uint32, a prefix sum of ceil(N_s / n_b)).
@@ -34,7 +36,8 @@
 namespace dg {
 namespace {
 
-constexpr size_t kNoAllocOffsets = (sizeof(Ctl) + 255) / 256 * 256;   // int64 visibility offsets [S+1]
+constexpr uint32_t kNoAllocCtls = 16;
+constexpr size_t kNoAllocOffsets = (kNoAllocCtls * sizeof(Ctl) + 255) / 256 * 256;   // int64 visibility offsets [S+1]
 constexpr size_t kNoAllocTileOffsets = kNoAllocOffsets + sizeof(int64_t) * (kNoAllocMaxSubgrids + 1);
 constexpr size_t kNoAllocUsed = kNoAllocTileOffsets + sizeof(uint32_t) * (kNoAllocMaxSubgrids + 1);
 static_assert(kNoAllocUsed <= kNoAllocBytes, "scratch layout exceeds the array");
@@ -80,7 +83,7 @@ __global__ __launch_bounds__(kSetupThreads) void noalloc_setup_kernel(unsigned c
 // ARGS: the offsets come as arguments, else from the scratch.
 template <int G, int F, bool ARGS>
 __global__ __launch_bounds__(kBlockThreads, 2) void degrid_noalloc_kernel(Problem pr, unsigned char* scr, int n_sub,
-                                                                          int n_tiles, int nb,
+                                                                          int n_tiles, int nb, Ctl* ctl,
                                                                           unsigned long long* oob_out,
                                                                           ArgOffsets args) {
     using GT = GridTraits<G>;
@@ -181,7 +184,6 @@ __global__ __launch_bounds__(kBlockThreads, 2) void degrid_noalloc_kernel(Proble
         wave_lds_sync();
     }
     if (oob_out) {   // the last workgroup hands the count over
-        Ctl* ctl = reinterpret_cast<Ctl*>(scr);
         if (finish_launch(ctl, wave_oob))
             *oob_out = *reinterpret_cast<volatile unsigned long long*>(&ctl->oob.v[2]);
     }
@@ -191,6 +193,7 @@ __global__ __launch_bounds__(kBlockThreads, 2) void degrid_noalloc_kernel(Proble
 struct NoAllocCall {
     Problem pr;
     unsigned char* scr;
+    Ctl* ctl;
     int n_sub, n_tiles, nb, blocks;
     unsigned long long* oob_out;
     const ArgOffsets* args;   // nullptr: the offsets are in the scratch
@@ -201,10 +204,10 @@ template <int G, int F>
 hipError_t launch_main(const NoAllocCall& c) {
     if (c.args)
         hipLaunchKernelGGL((degrid_noalloc_kernel<G, F, true>), dim3(c.blocks), dim3(kBlockThreads), 0, c.stream,
-                           c.pr, c.scr, c.n_sub, c.n_tiles, c.nb, c.oob_out, *c.args);
+                           c.pr, c.scr, c.n_sub, c.n_tiles, c.nb, c.ctl, c.oob_out, *c.args);
     else
         hipLaunchKernelGGL((degrid_noalloc_kernel<G, F, false>), dim3(c.blocks), dim3(kBlockThreads), 0, c.stream,
-                           c.pr, c.scr, c.n_sub, c.n_tiles, c.nb, c.oob_out, ArgOffsets{});
+                           c.pr, c.scr, c.n_sub, c.n_tiles, c.nb, c.ctl, c.oob_out, ArgOffsets{});
     return hipGetLastError();
 }
 
@@ -254,11 +257,13 @@ struct DeviceState {
     unsigned char* scratch = nullptr;
     int n_cu = 0;
     int occ[9] = {};
+    uint32_t next_ctl = 0;
 };
 std::mutex g_mutex;
 DeviceState g_dev[kMaxDevices];
 
-hipError_t device_state(int grid_kind, int gcf_kind, unsigned char** scr, int* resident) {
+// ctl, if given, receives the next control block.
+hipError_t device_state(int grid_kind, int gcf_kind, unsigned char** scr, int* resident, Ctl** ctl = nullptr) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
@@ -282,6 +287,7 @@ hipError_t device_state(int grid_kind, int gcf_kind, unsigned char** scr, int* r
     }
     *scr = d.scratch;
     *resident = d.n_cu * occ;
+    if (ctl) *ctl = reinterpret_cast<Ctl*>(d.scratch) + d.next_ctl++ % kNoAllocCtls;
     return hipSuccess;
 }
 
@@ -298,7 +304,7 @@ hipError_t launch_degrid_noalloc(const Problem& pr, int grid_kind, int gcf_kind,
     if (n_sub < 0 || n_sub > kNoAllocMaxSubgrids || nb < 1 || nb > kMaxNb) return hipErrorInvalidValue;
     NoAllocCall c{};
     int resident = 0;
-    hipError_t e = device_state(grid_kind, gcf_kind, &c.scr, &resident);
+    hipError_t e = device_state(grid_kind, gcf_kind, &c.scr, &resident, oob_out ? &c.ctl : nullptr);
     if (e != hipSuccess) return e;
     c.pr = pr;
     c.n_sub = (int)n_sub;
