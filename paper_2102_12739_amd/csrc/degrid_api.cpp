@@ -526,10 +526,12 @@ void settle(const dg_plan_* p) {
     if (p->launched) (void)hipDeviceSynchronize();
 }
 
-dg_status rebuild_tiles(dg_plan_* p, int32_t n_b_req, hipStream_t stream) {
+// The plan's tiles for a kernel variant and tile size. A failure leaves the tiles
+// and the variant as they were (they belong together), or no tiles.
+dg_status rebuild_tiles(dg_plan_* p, int32_t variant, int32_t n_b_req, hipStream_t stream) {
     settle(p);
-    const int box = degrid_variant_box_bytes(p->variant);
-    const int32_t n_b = std::min<int32_t>(n_b_req, degrid_variant_max_nb(p->variant));
+    const int box = degrid_variant_box_bytes(variant);
+    const int32_t n_b = std::min<int32_t>(n_b_req, degrid_variant_max_nb(variant));
     int64_t plain_tiles = 0;   // tiles of n_b visibilities, before building any
     for (int64_t s = 0; s < p->n_sub; ++s) plain_tiles += (p->offsets[s + 1] - p->offsets[s] + n_b - 1) / n_b;
     if (plain_tiles > 0x7FFFFFFF)
@@ -545,6 +547,7 @@ dg_status rebuild_tiles(dg_plan_* p, int32_t n_b_req, hipStream_t stream) {
         if (s != DG_OK) return s;
         q = split_queues(tiles);
     }
+    p->variant = variant;
     p->n_b_req = n_b_req;
     p->n_b = n_b;
     p->version++;
@@ -665,7 +668,7 @@ dg_status sort_plan(dg_plan p, const double* uvw, bool gridding, hipStream_t str
         if (p->d_perm) {
             (void)hipDeviceSynchronize();
             free_order(p);
-            return rebuild_tiles(p, p->n_b_req, stream);
+            return rebuild_tiles(p, p->variant, p->n_b_req, stream);
         }
         return DG_OK;
     }
@@ -673,13 +676,13 @@ dg_status sort_plan(dg_plan p, const double* uvw, bool gridding, hipStream_t str
     if (n == 0) return DG_OK;
     if (fault_injected("alloc")) return fail(DG_ERR_NOMEM, "allocation failure injected (DG_FAULT_INJECT=alloc)");
     dg_status st = build_order(p, uvw, gridding, stream);
-    if (st == DG_OK) st = rebuild_tiles(p, p->n_b_req, stream);
+    if (st == DG_OK) st = rebuild_tiles(p, p->variant, p->n_b_req, stream);
     if (st == DG_OK) return DG_OK;
     // no half-built order: back to input order (the tile list with it)
     const std::string why = g_last_error;
     (void)hipDeviceSynchronize();
     free_order(p);
-    (void)rebuild_tiles(p, p->n_b_req, stream);
+    (void)rebuild_tiles(p, p->variant, p->n_b_req, stream);
     g_last_error = why;
     return st;
 }
@@ -710,8 +713,7 @@ dg_status degrid_plan(const dg_desc* d, int64_t n_subgrids, const int64_t* vis_o
     }
     p->grid_div = grid_div;
     if (!variant_allowed(*d, variant)) variant = kDeepVariant;
-    p->variant = variant;
-    if (s == DG_OK) s = rebuild_tiles(p, n_b, stream);
+    if (s == DG_OK) s = rebuild_tiles(p, variant, n_b, stream);
     if (s != DG_OK) {
         free_scratch(p->ds);
         delete p;
@@ -968,8 +970,7 @@ dg_status degrid_tune(dg_plan p, const void* subgrids, const void* g_uv, const v
     for (int var = 0; var < degrid_variant_count() && st == DG_OK; ++var) {
         if (!variant_allowed(p->desc, var)) continue;
         for (int32_t nb : kCandidates) {
-            p->variant = var;
-            st = rebuild_tiles(p, nb, stream);
+            st = rebuild_tiles(p, var, nb, stream);
             if (st != DG_OK) break;
             for (int32_t div : kGridDivs) {
                 p->grid_div = div;
@@ -993,9 +994,8 @@ dg_status degrid_tune(dg_plan p, const void* subgrids, const void* g_uv, const v
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (st != DG_OK) return st;
-    p->variant = best_var;
     p->grid_div = best_div;
-    st = rebuild_tiles(p, best_nb, stream);
+    st = rebuild_tiles(p, best_var, best_nb, stream);
     if (st != DG_OK) return st;
     tune_cache_store(tune_key(p), best_nb, best_var, best_div);
     return DG_OK;
@@ -1017,8 +1017,7 @@ dg_status degrid_plan_set_kernel(dg_plan p, int32_t kernel, int32_t n_b, hipStre
     if (kernel >= 0 && !variant_allowed(p->desc, kernel))
         return fail(DG_ERR_UNSUPPORTED, "subgrids with %d w planes need kernel %d or %d (got %d)", p->desc.n_w,
                     kDeepVariant, kD1Variant, kernel);
-    if (kernel >= 0) p->variant = kernel;
-    return rebuild_tiles(p, n_b > 0 ? n_b : p->n_b_req, stream);
+    return rebuild_tiles(p, kernel >= 0 ? kernel : p->variant, n_b > 0 ? n_b : p->n_b_req, stream);
 }
 
 dg_status degrid_destroy(dg_plan p) {
@@ -1227,10 +1226,7 @@ dg_status degrid_batch_tune(const dg_plan* plans, int32_t n, const void* const* 
             const int32_t nb = std::min<int32_t>(nb_req, degrid_variant_max_nb(var));
             if (nb == last_nb) continue;   // the variant caps the tile size
             last_nb = nb;
-            for (int32_t i = 0; i < n && st == DG_OK; ++i) {
-                plans[i]->variant = var;
-                st = rebuild_tiles(plans[i], nb, stream);
-            }
+            for (int32_t i = 0; i < n && st == DG_OK; ++i) st = rebuild_tiles(plans[i], var, nb, stream);
             if (st != DG_OK) break;
             for (int32_t div : kGridDivs) {
                 plans[0]->grid_div = div;   // the batch's grid follows plan 0
@@ -1256,9 +1252,8 @@ dg_status degrid_batch_tune(const dg_plan* plans, int32_t n, const void* const* 
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     for (int32_t i = 0; i < n; ++i) {
-        plans[i]->variant = best_var;
         plans[i]->grid_div = best_div;
-        const dg_status s2 = rebuild_tiles(plans[i], best_nb, stream);
+        const dg_status s2 = rebuild_tiles(plans[i], best_var, best_nb, stream);
         if (st == DG_OK) st = s2;
     }
     if (st != DG_OK) return st;
