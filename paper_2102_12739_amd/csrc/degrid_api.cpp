@@ -829,6 +829,7 @@ dg_status grid_adjoint(dg_plan p, const void* vis, const void* g_uv, const void*
         op.n_tasks = p->own_tasks;
         op.n_split = p->own_counts.n_split;
         op.n_slices = p->own_counts.n_slices;
+        op.n_shared = p->own_counts.n_shared;
         op.ctl = p->d_own_ctl;
         op.accumulate = accumulate;
         op.nby = p->own.nby;

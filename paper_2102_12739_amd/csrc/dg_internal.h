@@ -128,19 +128,26 @@ static_assert(sizeof(OwnerTask) == 16, "OwnerTask must stay 16 bytes");
 // With W = places times slabs: runs are cut where the longest exceeds W /
 // kOwnerEven + kOwnerJoin. W / 2844 is a wavefront's even share of all runs at 16
 // per CU, where a visibility takes 0.23 us, and kOwnerJoin (15 us) stands for the
-// workspace and the join. 8 subgrids of 283 x 266 with 400 000 visibilities (longest
-// about 450) 71 us whole, 121 cut; 3 of 430 x 176 with 400 000 (1150) 135 and 93; 3
-// of 188 x 162 with 100 000 (700) 87 and 46. Longest slice: the larger of
-// kOwnerMinSlice and W / kOwnerSlices, whole batches of 64 (60 000 visibilities on
-// one spot: 44 us with 128, 50 with 256; 1.0 M dense at the centres of 16 subgrids:
-// 169 us with W / 2048, 225 with W / 1024). At most kOwnerMaxSlices can come of that:
-// the runs are together at most 2 W (a window reaches two segments at most), and
-// cutting adds at most one slice per run longer than a slice.
+// workspace and the join. Whole and cut (us): 8 subgrids of 283 x 266 with 400 000
+// visibilities (longest about 450) 72 and 96, 4 of 256 x 256 with 64 000 (190) 32
+// and 38; with 128 000 (330) 52 and 45, 3 of 430 x 176 with 400 000 (1150) 136 and
+// 81, 3 of 188 x 162 with 100 000 (700) 87 and 37. Stacks of more than 4 slabs mostly
+// skip visibilities, which gains less from few wavefronts per CU: kOwnerEvenDeep and
+// kOwnerJoinDeep (20 000 on 32 x 32 x 2000 530 us, with the others 713).
+// Longest slice: the larger of kOwnerMinSlice and W / kOwnerSlices, whole batches of
+// 64 (60 000 visibilities on one spot 40 us, with 64 52 and with 256 50; 1.0 M dense
+// at the centres of 16 subgrids 157 us, with W / 1024 216 and with W / 4096 167). At
+// most kOwnerMaxSlices can come of that: the runs are together at most 2 W (a window
+// reaches two segments at most), and cutting adds at most one slice per run longer
+// than a slice.
 constexpr int kOwnerMinSlice = 128;
 constexpr int kOwnerSlices = 2048;
 constexpr int kOwnerMaxSlices = 4 * kOwnerSlices;
 constexpr int kOwnerEven = 1280;
+constexpr int kOwnerEvenDeep = 2048;
 constexpr int kOwnerJoin = 150;
+constexpr int kOwnerJoinDeep = 400;
+constexpr int kOwnerShared = 16;   // slices that one wavefront of the join pass adds by itself
 struct alignas(16) OwnerSlice {
     uint32_t begin, end;   // positions of the owner order
     int32_t band;          // subgrid * nby + band
@@ -158,6 +165,7 @@ struct OwnerCounts {
     int64_t columns;      // of all slices
     int32_t n_split;      // tasks cut into slices: the first of the list
     int32_t n_slices;
+    int32_t n_shared;     // of the split tasks, the first: more than kOwnerShared slices
 };
 
 // Plans of at most this many visibilities have no records: the owner pass reads the
@@ -184,6 +192,7 @@ struct OwnerParams {
     int32_t nby;                   // bands per subgrid
     int32_t segment;               // columns of a segment
     int32_t n_slabs;               // slabs of w planes
+    int32_t n_shared;              // OwnerCounts
 };
 
 // Table-gradient pass: dL/dG_uv and dL/dG_w from dL/dV over the tiles of a
