@@ -244,7 +244,7 @@ dg_status degrid_residual(dg_plan p, const void* subgrids, const void* g_uv, con
  * bits on every call; visibilities whose coordinates
  * moved since the sort are added by a second pass with float32 atomics (so
  * when some moved, their sums' last bits vary from run to run). On
- * a plan in input order, and on subgrids of more than 1600 w planes, the output is zeroed (by a kernel) and contributions
+ * a plan in input order, and on subgrids of more than 3072 w planes, the output is zeroed (by a kernel) and contributions
  * are added with float32 atomics, so the last bits vary from run to run.
  * Asynchronous on 'stream'; allocates nothing.
  */

@@ -92,11 +92,12 @@ struct LaunchParams {
 // window reaches.
 constexpr int kOwnerBand = 16;            // rows of a band
 constexpr int kOwnerMaxSegment = 112;     // columns of a segment, at most
-// w planes of a subgrid, at most: every slab's task walks all visibilities of its
-// band and segment, so deeper stacks scatter instead (400 000 visibilities on 128 x
-// 128: 512 planes 1259 us, scattered 5089; 1536 planes 3878 and 5180; 3000 planes
-// 6625 and 5437; 20 000 on 32 x 32: 1536 planes 461 and 563; 2000 planes 717 and 566).
-constexpr int kOwnerMaxPlanes = 1600;
+// w planes of a subgrid, at most: every slab's task walks the visibilities of its
+// band and segment, and writes 32 bytes of each cell, so deeper stacks scatter
+// instead (owners and scattered, us: 100 000 visibilities on 4 subgrids of 64 x 64 x
+// 3000 384 and 2721, x 8000 994 and 2958; 1000 on 64 x 64 x 2000 42 and 53, x 8000
+// 126 and 85).
+constexpr int kOwnerMaxPlanes = 3072;
 constexpr uint32_t kNoPlace = 0xFFFFFFFFu;
 
 struct OwnerPlaces {
@@ -131,9 +132,7 @@ static_assert(sizeof(OwnerTask) == 16, "OwnerTask must stay 16 bytes");
 // workspace and the join. Whole and cut (us): 8 subgrids of 283 x 266 with 400 000
 // visibilities (longest about 450) 72 and 96, 4 of 256 x 256 with 64 000 (190) 32
 // and 38; with 128 000 (330) 52 and 45, 3 of 430 x 176 with 400 000 (1150) 136 and
-// 81, 3 of 188 x 162 with 100 000 (700) 87 and 37. Stacks of more than 4 slabs mostly
-// skip visibilities, which gains less from few wavefronts per CU: kOwnerEvenDeep and
-// kOwnerJoinDeep (20 000 on 32 x 32 x 2000 530 us, with the others 713).
+// 81, 3 of 188 x 162 with 100 000 (700) 87 and 37.
 // Longest slice: the larger of kOwnerMinSlice and W / kOwnerSlices, whole batches of
 // 64 (60 000 visibilities on one spot 40 us, with 64 52 and with 256 50; 1.0 M dense
 // at the centres of 16 subgrids 157 us, with W / 1024 216 and with W / 4096 167). At
@@ -144,9 +143,7 @@ constexpr int kOwnerMinSlice = 128;
 constexpr int kOwnerSlices = 2048;
 constexpr int kOwnerMaxSlices = 4 * kOwnerSlices;
 constexpr int kOwnerEven = 1280;
-constexpr int kOwnerEvenDeep = 2048;
 constexpr int kOwnerJoin = 150;
-constexpr int kOwnerJoinDeep = 400;
 constexpr int kOwnerShared = 16;   // slices that one wavefront of the join pass adds by itself
 struct alignas(16) OwnerSlice {
     uint32_t begin, end;   // positions of the owner order
@@ -172,9 +169,11 @@ struct OwnerCounts {
 // visibilities themselves, and the fix-up pass checks every one. That is one launch
 // less, on the host too, and more scattered reads (records and direct): 2 subgrids
 // with 8000 visibilities 20.7 and 14.8 us, 16 with 32 000 36.8 and 33.2, with
-// 128 000 47.9 and 45.0, with 512 000 88.3 and 95.5; 12 planes, 4 subgrids with
-// 32 000 50.9 and 49.5, with 128 000 79.9 and 80.4, with 256 000 112 and 118.
+// 128 000 47.9 and 45.0, with 512 000 88.3 and 95.5. Every slab reads them again: at
+// most kOwnerDirectWork visibilities times slabs (100 000 visibilities on 4 subgrids
+// of 64 x 64 x 256: 352 and 398 us).
 constexpr int64_t kOwnerDirect = 1 << 17;
+constexpr int64_t kOwnerDirectWork = 1 << 18;
 
 struct OwnerParams {
     Problem prob;                  // g_uv, g_w, vis (input), grid_out; uvw without records

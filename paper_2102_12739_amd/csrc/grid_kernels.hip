@@ -219,7 +219,10 @@ __global__ __launch_bounds__(kBlockThreads) void grid_adjoint_kernel(LaunchParam
 // planes outside its taps).
 //
 // DEEP: subgrids with more than four w planes; a segment covers planes 4 slab
-// .. 4 slab + 3, and c is 0 for planes outside the visibility's four taps.
+// .. 4 slab + 3, and c is 0 for planes outside the visibility's four taps. A
+// visibility reaches one or two slabs, so of each 64 those that reach this one are
+// brought together first (320 000 on 8 subgrids of 256 x 256 x 16: 132 us without
+// that, with it 105; 100 000 on 4 of 64 x 64 x 256 346 and 78).
 
 typedef float F32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t U32x4 __attribute__((ext_vector_type(4)));
@@ -528,7 +531,7 @@ __global__ __launch_bounds__(kOwnerMaxWaves* kWave) void grid_owner_kernel(Owner
             } else {
                 x = nxt;
             }
-            const int n = (int)min((uint32_t)kWave, end - pos);
+            int n = (int)min((uint32_t)kWave, end - pos);
             if (pos + kWave < end) nxt = fetch(pos + kWave);
             int flags = 0, at = 0, dz = 0;
             float c[kOwnerRec];
@@ -562,8 +565,20 @@ __global__ __launch_bounds__(kOwnerMaxWaves* kWave) void grid_owner_kernel(Owner
             bool odd = bad_table;
 #pragma unroll
             for (int q = 0; q < kOwnerRec; ++q) odd = odd || !isfinite(c[q]);
-            *reinterpret_cast<float4*>(rec + lane * kOwnerRec) = make_float4(c[0], c[1], c[2], c[3]);
-            *reinterpret_cast<float4*>(rec + lane * kOwnerRec + 4) = make_float4(c[4], c[5], c[6], c[7]);
+            int slot = lane;
+            if constexpr (DEEP) {
+                // those that reach this slab first, in their order
+                const uint64_t mine = __ballot(flags != 0);
+                const int before = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mine >> 32),
+                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0u));
+                n = (int)__popcll(mine);
+                slot = flags != 0 ? before : n + lane - before;
+                flags = __builtin_amdgcn_ds_permute(slot * 4, flags);
+                at = __builtin_amdgcn_ds_permute(slot * 4, at);
+                dz = __builtin_amdgcn_ds_permute(slot * 4, dz);
+            }
+            *reinterpret_cast<float4*>(rec + slot * kOwnerRec) = make_float4(c[0], c[1], c[2], c[3]);
+            *reinterpret_cast<float4*>(rec + slot * kOwnerRec + 4) = make_float4(c[4], c[5], c[6], c[7]);
             wave_lds_sync();
 
             // one visibility under its window's mask (values not finite)

@@ -175,9 +175,7 @@ __device__ void cut_tasks(const OwnerShape& h, const Key* keys, int64_t n_slots,
     const int64_t share = max((work + kOwnerSlices - 1) / kOwnerSlices, (int64_t)kOwnerMinSlice);
     const uint32_t longest = (uint32_t)((share + kWave - 1) / kWave * kWave);
     // weights are complements and include the columns (at most h.segment)
-    const bool deep = h.n_slabs > 4;
-    const int64_t even = work / (deep ? kOwnerEvenDeep : kOwnerEven) + (deep ? kOwnerJoinDeep : kOwnerJoin);
-    const bool uneven = ~weights[0] > even + h.segment;
+    const bool uneven = ~weights[0] > work / kOwnerEven + kOwnerJoin + h.segment;
     int64_t n_split = uneven ? lower_bound(weights, n_tasks, ~(longest + (uint32_t)h.segment)) : 0;
     const uint32_t many = (uint32_t)min((int64_t)0x7FFFFFFF, (int64_t)longest * kOwnerShared + h.segment);
     const int64_t n_shared = min(n_split, lower_bound(weights, n_tasks, ~many));

@@ -11,7 +11,7 @@ from tests.gpu_common import REL_L2_FP32, announce, device, plan_for, rel_l2, up
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n_w", [1599, 1600, 1601])
+@pytest.mark.parametrize("n_w", [300, 3071, 3072, 3073])
 def test_deepest_stacks(n_w):
     announce(f"depth {n_w}")
     p = wl.make_problem("depth", [900, 0, 700], seed=n_w, kind="uniform", n_v=17, n_u=20, n_w=n_w)
