@@ -623,7 +623,7 @@ dg_status build_order(dg_plan_* p, const double* uvw, bool gridding, hipStream_t
     h.n_seg = (d.n_u + h.segment - 1) / h.segment;
     h.direct = h.n_vis <= kOwnerDirect && h.n_vis * h.n_slabs <= kOwnerDirectWork;
     // too deep, or outside what its positions and tasks can name: the adjoint scatters
-    if (d.n_w > kOwnerMaxPlanes || h.n_vis > 0x7FFFFFFF || h.tasks() > 0x7FFFFFFF) {
+    if (d.n_w > kOwnerMaxPlanes || h.n_vis > kOwnerMaxVis || h.tasks() > 0x7FFFFFFF) {
         e = hipStreamSynchronize(stream);
         return e == hipSuccess ? DG_OK : hip_fail(e, "sorting the work order");
     }

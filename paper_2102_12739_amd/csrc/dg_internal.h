@@ -99,6 +99,10 @@ constexpr int kOwnerMaxSegment = 112;     // columns of a segment, at most
 // 126 and 85).
 constexpr int kOwnerMaxPlanes = 3072;
 constexpr uint32_t kNoPlace = 0xFFFFFFFFu;
+// visibilities, at most: the positions of their two places each, and a batch past
+// the last of them, are 32-bit
+constexpr int64_t kOwnerMaxVis = 0x7FFFFF00;
+static_assert(2 * kOwnerMaxVis + kWave <= (int64_t)kNoPlace, "a run's last batch ends within 32 bits");
 
 struct OwnerPlaces {
     uint32_t first, second;   // positions in the owner order, or kNoPlace
