@@ -437,10 +437,12 @@ __global__ void set_f64_kernel(double* p, double v) {
     if (threadIdx.x == 0) *p = v;
 }
 
-__global__ void zero_kernel(float4* p, int64_t n) {
+// n pairs of complex values, and one more when odd.
+__global__ void zero_kernel(float4* p, int64_t n, bool odd) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
-        p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t i = first; i < n; i += stride) p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (odd && first == 0) *reinterpret_cast<float2*>(p + n) = make_float2(0.f, 0.f);
 }
 
 template <int G, int F, int V>
@@ -551,11 +553,12 @@ hipError_t launch_set_f64(double* p, double v, hipStream_t stream) {
 
 hipError_t launch_zero(void* ptr, int64_t bytes, hipStream_t stream) {
     if (bytes <= 0) return hipSuccess;
-    if (bytes % 16 != 0) return hipErrorInvalidValue;
+    if (bytes % 8 != 0) return hipErrorInvalidValue;
     const int64_t n = bytes / 16;
-    int64_t blocks = (n + 255) / 256;
+    int64_t blocks = n / 256 + 1;
     if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(zero_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, static_cast<float4*>(ptr), n);
+    hipLaunchKernelGGL(zero_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, static_cast<float4*>(ptr), n,
+                       bytes % 16 != 0);
     return hipGetLastError();
 }
 
