@@ -274,7 +274,7 @@ dg_status degrid_oob_count(dg_plan p, int64_t* count);
  * visibility's sum does not depend on the order); only speed depends on uvw
  * matching the coordinates passed to later calls. Allocates the plan's
  * orders and the adjoint's workspace (about 45 bytes per visibility; 20 up to
- * 2^17 visibilities, more for the columns where they crowd) and temporary sort
+ * 196 608 visibilities, more for the columns where they crowd) and temporary sort
  * buffers. Where the device has no memory for the adjoint's part, the call
  * succeeds as degrid_plan_sort_forward does. Synchronises 'stream'.
  * DG_ERR_UNSUPPORTED if N >= 2^32.

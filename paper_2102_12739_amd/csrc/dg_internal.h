@@ -132,11 +132,12 @@ static_assert(sizeof(OwnerTask) == 16, "OwnerTask must stay 16 bytes");
 //
 // With W = places times slabs: runs are cut where the longest exceeds W /
 // kOwnerEven + kOwnerJoin. W / 2844 is a wavefront's even share of all runs at 16
-// per CU, where a visibility takes 0.23 us, and kOwnerJoin (15 us) stands for the
-// workspace and the join. Whole and cut (us): 8 subgrids of 283 x 266 with 400 000
-// visibilities (longest about 450) 72 and 96, 4 of 256 x 256 with 64 000 (190) 32
-// and 38; with 128 000 (330) 52 and 45, 3 of 430 x 176 with 400 000 (1150) 136 and
-// 81, 3 of 188 x 162 with 100 000 (700) 87 and 37.
+// per CU, where a visibility takes 0.23 us, and kOwnerJoin (22 us) stands for the
+// workspace and the join, a launch more on the host. Whole and cut (us): 8 subgrids
+// of 283 x 266 with 400 000 visibilities (longest about 450) 72 and 96, 4 of 256 x
+// 256 with 64 000 (190) 32 and 38, with 128 000 (330) 52 and 45 (not enough where the
+// host sets the pace); 4 of 512 x 512 with 16 000 at their centres 49 and 32, 3 of
+// 430 x 176 with 400 000 (1150) 136 and 81, 3 of 188 x 162 with 100 000 (700) 87 and 37.
 // Longest slice: the larger of kOwnerMinSlice and W / kOwnerSlices, whole batches of
 // 64 (60 000 visibilities on one spot 40 us, with 64 52 and with 256 50; 1.0 M dense
 // at the centres of 16 subgrids 157 us, with W / 1024 216 and with W / 4096 167). At
@@ -147,7 +148,7 @@ constexpr int kOwnerMinSlice = 128;
 constexpr int kOwnerSlices = 2048;
 constexpr int kOwnerMaxSlices = 4 * kOwnerSlices;
 constexpr int kOwnerEven = 1280;
-constexpr int kOwnerJoin = 150;
+constexpr int kOwnerJoin = 220;
 constexpr int kOwnerShared = 16;   // slices that one wavefront of the join pass adds by itself
 struct alignas(16) OwnerSlice {
     uint32_t begin, end;   // positions of the owner order
@@ -173,10 +174,10 @@ struct OwnerCounts {
 // visibilities themselves, and the fix-up pass checks every one. That is one launch
 // less, on the host too, and more scattered reads (records and direct): 2 subgrids
 // with 8000 visibilities 20.7 and 14.8 us, 16 with 32 000 36.8 and 33.2, with
-// 128 000 47.9 and 45.0, with 512 000 88.3 and 95.5. Every slab reads them again: at
-// most kOwnerDirectWork visibilities times slabs (100 000 visibilities on 4 subgrids
-// of 64 x 64 x 256: 352 and 398 us).
-constexpr int64_t kOwnerDirect = 1 << 17;
+// 128 000 47.9 and 45.0, with 256 000 62.5 and 64.1, with 512 000 88.3 and 95.5.
+// Every slab reads them again: at most kOwnerDirectWork visibilities times slabs
+// (100 000 visibilities on 4 subgrids of 64 x 64 x 256: 352 and 398 us).
+constexpr int64_t kOwnerDirect = 3 << 16;
 constexpr int64_t kOwnerDirectWork = 1 << 18;
 
 struct OwnerParams {

@@ -1,4 +1,4 @@
-"""The owner-computes adjoint on both sides of the number of visibilities (2^17)
+"""The owner-computes adjoint on both sides of the number of visibilities (3 * 2^16)
 up to which it reads the visibilities themselves instead of records of them:
 every table type and path, deep stacks, moved and out-of-range coordinates,
 accumulation and values that are not finite, against the FP64 oracle."""
@@ -13,7 +13,7 @@ from tests.gpu_common import REL_L2_FP32, announce, device, plan_for, rel_l2, st
 
 pytestmark = pytest.mark.gpu
 
-DIRECT = 1 << 17
+DIRECT = 3 << 16
 
 
 @pytest.mark.parametrize("n", [DIRECT, DIRECT + 1])
